@@ -96,6 +96,9 @@ struct alignas(64) HostCtl {
   uint32_t alive[kAliveWords];  // bit per actor
 };
 
+constexpr uint32_t kBells = 16;
+constexpr uint32_t kLeaveAll = 0xFFFFFFFFu;  // a drainer saw the host's stop flag
+
 // Device-resident control block (agent-scope atomics only).  The hot
 // counters sit on separate 128-byte lines (the L2 line size).
 struct alignas(128) DevCtl {
@@ -110,13 +113,20 @@ struct alignas(128) DevCtl {
   uint64_t comp_tail;      // completion positions handed out
   uint8_t p4[120];
   uint64_t drained;        // mailbox entries drained
-  uint32_t stop_seen;      // a drainer saw the host's stop flag
   uint32_t wg_exited[2];   // by launch parity: workgroups that left
-  uint32_t retiring[2];    // by launch parity: generation that began to retire
   uint32_t backlog;        // the last drain pass left entries in the mailbox
-  uint8_t p5[96];
+  uint8_t p5[108];
+  // What a workgroup without work polls: copies of the published count and of
+  // the signs to leave, each on a line of its own, so that the line the
+  // drainer and the claimers work on is not read by every idle workgroup.
+  // Written by the holder of the drain lock only.
+  struct alignas(128) Bell {
+    uint64_t pub;       // 2 * tiles_pub + (the mailbox holds a backlog)
+    uint32_t leave[2];  // by launch parity: the generation that retires, or kLeaveAll
+    uint8_t pad[112];
+  } bell[kBells];
 };
-static_assert(sizeof(DevCtl) == 6 * 128, "hot counters on separate 128-byte lines");
+static_assert(sizeof(DevCtl) == (6 + kBells) * 128, "hot counters on separate 128-byte lines");
 
 constexpr uint32_t kNopTile = 0xFFFFFFFFu;  // tile-map entry of a filler tile
 

@@ -101,7 +101,7 @@ __device__ __forceinline__ void st_dev_rel(T* p, T v) {
 }
 template <typename T>
 __device__ __forceinline__ bool cas_dev(T* p, T& expected, T desired) {
-  return __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_ACQ_REL,
+  return __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_ACQUIRE,
                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -141,6 +141,17 @@ __device__ void write_completion(KArgsC& a, uint64_t req_id, int32_t status,
   write_completion_at(a, pos, req_id, status, data);
 }
 
+// Waits until this wave's stores have reached the point where their scope
+// makes them visible (memory, for the scoped stores above).
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Tells the idle workgroups the published count and whether the mailbox holds
+// a backlog (thread-level, drain lock held, after the publication's release).
+__device__ __forceinline__ void ring_bells(KArgsC& a, uint64_t pub, uint32_t backlog) {
+  const uint64_t v = 2 * pub + backlog;
+  for (uint32_t i = 0; i < kBells; ++i) st_dev(&a.dctl->bell[i].pub, v);
+}
+
 // Appends `nt` tiles of slot `slot` to the global tile sequence (caller
 // holds the drain lock).  Returns false if the tile map has no room within
 // the wait bound.
@@ -155,7 +166,8 @@ __device__ bool publish_tiles_locked(KArgsC& a, uint32_t slot, uint32_t nt) {
   a.slots[slot].ntiles = nt;
   for (uint32_t t = 0; t < nt; ++t) a.tile2slot[(pub + t) & (kTileMapCap - 1)] = slot;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  st_dev_rel(&a.dctl->tiles_pub, pub + nt);
+  st_dev(&a.dctl->tiles_pub, pub + nt);
+  ring_bells(a, pub + nt, ld_dev(&a.dctl->backlog));
   return true;
 }
 
@@ -170,7 +182,13 @@ __device__ __forceinline__ bool lock_drain(KArgsC& a, bool bounded) {
   }
 }
 
-__device__ void unlock_drain(KArgsC& a) { st_dev_rel(&a.dctl->drain_lock, 0u); }
+// What the lock protects is either written with scoped stores, which this
+// waits for, or released by the fence before a publication: no second
+// writeback of the L2 here.
+__device__ void unlock_drain(KArgsC& a) {
+  wait_stores();
+  st_dev(&a.dctl->drain_lock, 0u);
+}
 
 // Pipeline stages small enough to run where the previous stage finished:
 // the workgroup that completes a message's last tile runs the next stage
@@ -540,6 +558,7 @@ struct DrainLds {
   uint32_t any_hash;  // some entry is one
   uint32_t any_echo;  // some entry is an inline echo
   uint64_t hpos;
+  uint32_t nbig;       // entries whose tile map the whole workgroup writes
   uint32_t first_bad;  // light launch: first entry it cannot run
   uint32_t any_dead;   // some entry's actor looked dead in the snapshot
   uint32_t alive[kAliveWords];
@@ -549,6 +568,7 @@ struct DrainLds {
   uint32_t wave_sum[4];
   uint64_t d, cnt, pub, done;
   uint32_t total;
+  uint32_t backlog;  // this pass leaves entries in the mailbox
   // set by a sentinel before its drain pass: the launch may retire if the
   // pass finds the mailbox empty and the drained count still equal to this
   // (checked under the drain lock)
@@ -706,6 +726,29 @@ __device__ void complete_hash_entries(KArgsC& a, DrainLds& L) {
   }
 }
 
+// This launch's workgroups leave once they hold no work (thread-level, drain
+// lock held).
+__device__ __forceinline__ void retire_launch(KArgsC& a) {
+  const uint32_t par = a.gen & 1u;
+  for (uint32_t i = 0; i < kBells; ++i) st_dev(&a.dctl->bell[i].leave[par], a.gen);
+  st_sys_rel(&a.hctl->retiring[par], a.gen);
+}
+
+// Releases the slots and tile map entries the workgroup wrote: once every
+// wave's stores are in this XCD's L2, one writeback by thread 0's wave covers
+// them all.  Also before a pass gives up: lines left dirty here would be
+// written back over a later message's slot.
+__device__ __forceinline__ void release_slots() {
+  wait_stores();
+  __syncthreads();
+  if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+}
+
+// Entries with more tiles than this have their part of the tile map written
+// by the whole workgroup: a single thread takes about 35 ns per tile (36 us
+// for the 790 tiles of a 1021 x 773 image, 300 us for 8,192).
+constexpr uint32_t kOwnMapTiles = 8;
+
 // Drains one batch from the mailbox (whole workgroup; the caller holds the
 // drain lock, which is released here).  Returns true if anything was drained.
 __device__ __forceinline__ bool drain_once_body(KArgsC& a, DrainLds& L, bool may_claim,
@@ -722,24 +765,36 @@ __device__ __forceinline__ bool drain_once_body(KArgsC& a, DrainLds& L, bool may
   if (t == 0) L.any_dead = 0;
   if (t == 0) L.any_hash = 0;
   if (t == 0) L.any_echo = 0;
+  if (t == 0) L.nbig = 0;
   if (t == 0) {
-    // All five loads are in flight together; one system-scope acquire fence
+    // All six loads are in flight together; one system-scope acquire fence
     // after them orders the entry reads below after the tail (each acquire
-    // load on its own would wait for its own round trip).
+    // load on its own would wait for its own round trip).  A look at an empty
+    // mailbox has nothing to order, and the fence would empty the L2 that the
+    // XCD's other workgroups work from.
     const uint32_t stop = ld_sys(&a.hctl->stop);
     const uint64_t tail = ld_sys(&a.hctl->tail);
     const uint64_t d = ld_dev(&a.dctl->drained);
     const uint64_t pubv = ld_dev(&a.dctl->tiles_pub);
     const uint64_t done = ld_dev(&a.dctl->tiles_done);
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
+    const uint32_t had_backlog = ld_dev(&a.dctl->backlog);
     const uint64_t avail = tail - d;
+    if (avail) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
     L.d = d;
     L.cnt = avail < a.max_batch ? avail : a.max_batch;
     // Lets idle workgroups help while a backlog remains (relaxed: a hint).
-    st_dev(&a.dctl->backlog, avail > a.max_batch ? 1u : 0u);
+    L.backlog = avail > a.max_batch ? 1u : 0u;
+    if (had_backlog != L.backlog) {
+      st_dev(&a.dctl->backlog, L.backlog);
+      ring_bells(a, pubv, L.backlog);
+    }
     L.pub = pubv;
     L.done = done;
-    if (stop) st_dev(&a.dctl->stop_seen, 1u);
+    if (stop)
+      for (uint32_t i = 0; i < kBells; ++i) {
+        st_dev(&a.dctl->bell[i].leave[0], kLeaveAll);
+        st_dev(&a.dctl->bell[i].leave[1], kLeaveAll);
+      }
   }
   if (t < kKeys) L.hist[t] = 0;
   if (t == 0) L.first_bad = ~0u;
@@ -752,9 +807,7 @@ __device__ __forceinline__ bool drain_once_body(KArgsC& a, DrainLds& L, bool may
       // of it leaves once it holds no work (claimed tiles are finished
       // first), and the host starts a new launch when messages arrive.
       if (L.retire_ok && L.d == L.retire_drained && ld_dev(&a.dctl->tiles_claimed) >= L.pub) {
-        const uint32_t par = a.gen & 1u;
-        st_dev(&a.dctl->retiring[par], a.gen);
-        st_sys_rel(&a.hctl->retiring[par], a.gen);
+        retire_launch(a);
       }
       unlock_drain(a);
     }
@@ -823,9 +876,9 @@ __device__ __forceinline__ bool drain_once_body(KArgsC& a, DrainLds& L, bool may
     // starts a full launch.
     cnt = L.first_bad;
     if (cnt == 0) {
+      release_slots();
       if (t == 0) {
-        st_dev(&a.dctl->retiring[a.gen & 1u], a.gen);
-        st_sys_rel(&a.hctl->retiring[a.gen & 1u], a.gen);
+        retire_launch(a);
         unlock_drain(a);
       }
       return false;
@@ -837,6 +890,7 @@ __device__ __forceinline__ bool drain_once_body(KArgsC& a, DrainLds& L, bool may
   if (cnt == 1) {
     // A single entry (the common case at low load): no scan, no grouping.
     if (L.nt[0] > room) {
+      release_slots();
       if (t == 0) unlock_drain(a);
       return false;
     }
@@ -860,6 +914,7 @@ __device__ __forceinline__ bool drain_once_body(KArgsC& a, DrainLds& L, bool may
       __syncthreads();
       cnt = (uint32_t)L.cnt;
       if (cnt == 0) {
+        release_slots();
         if (t == 0) unlock_drain(a);
         return false;
       }
@@ -917,8 +972,18 @@ __device__ __forceinline__ bool drain_once_body(KArgsC& a, DrainLds& L, bool may
     const uint64_t base = pub + L.scan[L.pos[i]];
     a.slots[slot].tile_base = base;
     a.slots[slot].ntiles = nt;
-    for (uint32_t k = 0; k < nt; ++k) a.tile2slot[(base + k) & (kTileMapCap - 1)] = slot;
+    if (nt <= kOwnMapTiles) {
+      for (uint32_t k = 0; k < nt; ++k) a.tile2slot[(base + k) & (kTileMapCap - 1)] = slot;
+    } else {
+      L.hactor[atomicAdd(&L.nbig, 1u)] = (uint16_t)i;  // free once the hash entries have run
+    }
     if (L.dead[i]) write_completion(a, a.slots[slot].d.req_id, CAF_E_QUIT, nullptr);
+  }
+  __syncthreads();
+  for (uint32_t b = 0; b < L.nbig; ++b) {
+    const uint32_t i = L.hactor[b], slot = L.slot[i], nt = L.nt[i];
+    const uint64_t base = pub + L.scan[L.pos[i]];
+    for (uint32_t k = t; k < nt; k += kThreads) a.tile2slot[(base + k) & (kTileMapCap - 1)] = slot;
   }
   if (L.any_echo) {
     // the inline echoes of the entries drained in this pass join the list
@@ -929,12 +994,9 @@ __device__ __forceinline__ bool drain_once_body(KArgsC& a, DrainLds& L, bool may
     __syncthreads();
   }
   complete_hash_entries(a, L);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  __syncthreads();
+  release_slots();
   if (t == 0) {
-    // The fence and barrier above release the slots and tile map written by
-    // every thread, so the tiles are published first, without another fence.
-    // The unlock releases the drained counts: the host copy must never move
+    // The unlock waits for the drained counts: the host copy must never move
     // backwards, so it lands before the next holder can write its own.
     // The drainer takes one index before the tiles become visible, so it
     // runs the first of them itself (a one-message pass is usually a reply
@@ -947,6 +1009,7 @@ __device__ __forceinline__ bool drain_once_body(KArgsC& a, DrainLds& L, bool may
       cl.own = cl.next >= pub && cl.next < pub + total;
     }
     st_dev(&a.dctl->tiles_pub, pub + total);
+    if (total) ring_bells(a, pub + total, L.backlog);
     st_dev(&a.dctl->drained, L.d + cnt);
     st_sys(&a.hctl->drained, L.d + cnt);
     unlock_drain(a);
@@ -1009,11 +1072,13 @@ __device__ void fill_reservations_locked(KArgsC& a) {
   if (cl <= pub) return;
   for (uint64_t i = pub; i < cl; ++i) a.tile2slot[i & (kTileMapCap - 1)] = kNopTile;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  st_dev_rel(&a.dctl->tiles_pub, cl);
+  st_dev(&a.dctl->tiles_pub, cl);
+  ring_bells(a, cl, ld_dev(&a.dctl->backlog));
 }
 
 enum : uint32_t { CMD_IDLE = 0, CMD_TILE = 1, CMD_DRAIN = 2 };
 constexpr uint32_t kSentinels = 16;
+constexpr uint32_t kHelpRounds = 4;
 
 template <bool kFull, int kBk = kBf16SliceK, bool kWide = false>
 __device__ __forceinline__ void drain_body(KArgsC& a) {
@@ -1026,6 +1091,9 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
   // they have not moved (thread 0; kept in LDS, not in registers)
   __shared__ uint64_t s_seen_drained, s_still_since;
   __shared__ uint32_t s_retire_ok;
+  // The claim cursor this workgroup last read: with no more than that
+  // published, its bell says so without a look at the counters themselves.
+  __shared__ uint64_t s_seen_cur;
   const uint32_t t = threadIdx.x;
   uint64_t last_work = now_ticks();
   // At the start of a launch only the sentinels try the drain lock: every
@@ -1033,7 +1101,10 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
   // its fences) that delays the first drain pass by microseconds.
   uint32_t idle_rounds = blockIdx.x < kSentinels ? 0u : 1u;
   Claim c;  // thread 0's reservation
+  uint32_t polls = 0;  // rounds without work since the last work (thread 0)
+  const auto* bell = &a.dctl->bell[blockIdx.x % kBells];
   if (t == 0) {
+    s_seen_cur = 0;
     s_seen_drained = ~0ull;
     s_still_since = last_work;
     s_retire_ok = 0;
@@ -1042,9 +1113,11 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
     if (t == 0) {
       uint32_t cmd = CMD_IDLE;
       uint64_t pub = 0;
-      if (c.next == c.end) {
+      const uint64_t rung = polls ? ld_dev(&bell->pub) : 0;
+      if (c.next == c.end && (polls == 0 || (rung >> 1) > s_seen_cur)) {
         const uint64_t pub0 = ld_dev(&a.dctl->tiles_pub);
         const uint64_t cur0 = ld_dev(&a.dctl->tiles_claimed);
+        s_seen_cur = cur0;
         // Drain ahead: while the mailbox holds more than one pass and the
         // published tiles nobody has claimed yet run low, this workgroup
         // takes the next pass now (one attempt at the lock), so that the
@@ -1065,8 +1138,9 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
         c.own = false;
         cmd = CMD_TILE;
       } else if (c.next < c.end) {
-        // the count read while reserving usually covers the new indices
-        if (c.next >= pub) pub = ld_dev(&a.dctl->tiles_pub);
+        // the count read while reserving usually covers the new indices; a
+        // holder of indices not yet published watches its bell
+        if (c.next >= pub) pub = polls ? rung >> 1 : ld_dev(&a.dctl->tiles_pub);
         if (c.next < pub) {
           const uint64_t n = (c.end < pub ? c.end : pub) - c.next;
           s_g = c.next;
@@ -1077,12 +1151,13 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
         }
       }
       // Draining an empty mailbox still holds the lock for a host round
-      // trip, so idle workgroups do not all poll it: the sentinels do, a
-      // workgroup that just finished work tries once, and so does one
-      // waiting for its reserved index to be published; everyone helps
-      // while the last pass left a backlog.
-      const bool may_drain = blockIdx.x < kSentinels || idle_rounds == 0 || c.next < c.end ||
-                             ld_dev(&a.dctl->backlog) != 0;
+      // trip, so idle workgroups do not all poll it: the sentinels do, and a
+      // workgroup that just finished work tries once; one waiting for its
+      // reserved index, and everyone while the last pass left a backlog, try
+      // every few rounds (the pass under way holds the lock meanwhile, and a
+      // thousand workgroups trying it slow that pass down).
+      const bool may_drain = blockIdx.x < kSentinels || idle_rounds == 0 ||
+                             ((c.next < c.end || (rung & 1)) && polls % kHelpRounds == 0);
       if (cmd == CMD_IDLE && may_drain && lock_drain(a, false)) cmd = CMD_DRAIN;
       s_cmd = cmd;
     }
@@ -1143,6 +1218,7 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
       }
       last_work = now_ticks();
       idle_rounds = 0;
+      polls = 0;
       continue;
     }
     if (cmd == CMD_DRAIN) {
@@ -1156,15 +1232,16 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
       if (got) {
         last_work = now_ticks();
         idle_rounds = 0;
+        polls = 0;
         continue;
       }
     }
     if (t == 0) {
       uint32_t ex = 0;
-      const uint32_t par = a.gen & 1u;
+      ++polls;
       const bool holding = c.next < c.end;  // reserved, not yet published
-      const bool leaving =
-          ld_dev(&a.dctl->stop_seen) || ld_dev(&a.dctl->retiring[par]) == a.gen;
+      const uint32_t lv = ld_dev(&bell->leave[a.gen & 1u]);
+      const bool leaving = lv == a.gen || lv == kLeaveAll;
       if (holding) {
         // Nobody may leave an index unexecuted: before this launch goes (or
         // once this workgroup has idled as long as a launch may linger),
