@@ -118,27 +118,25 @@ __device__ __forceinline__ bool actor_alive(const HostCtl* h, uint32_t actor) {
 // ---- completion -------------------------------------------------------------
 
 // Publishes one reply notification to the host at completion position
-// `pos` (thread-level).
-__device__ void write_completion_at(KArgsC& a, uint64_t pos, uint64_t req_id, int32_t status,
-                                    const uint8_t* data) {
+// `pos` (thread-level), after releasing what was written before it.  `inl`:
+// the 16 bytes of a reply that travels inline, else nullptr.
+__device__ __forceinline__ void write_completion_at(KArgsC& a, uint64_t pos, uint64_t req_id,
+                                                    int32_t status, const uint64_t* inl) {
   Comp* c = &a.comp[pos & (a.ccap - 1u)];  // ccap is a power of two
-  st_sys(&c->req_id, req_id);
-  st_sys(&c->status, status);
-  uint32_t* dst = reinterpret_cast<uint32_t*>(c->data);
-  for (int i = 0; i < 4; ++i) {
-    uint32_t v = 0;
-    if (data) v = reinterpret_cast<const uint32_t*>(data)[i];
-    st_sys(dst + i, v);
+  if (inl) {
+    uint64_t* dst = reinterpret_cast<uint64_t*>(c->data);
+    st_sys(dst, inl[0]);
+    st_sys(dst + 1, inl[1]);
   }
-  st_sys_rel(&c->lap, (uint32_t)(pos >> __builtin_ctz(a.ccap)) + 1u);
+  st_sys_rel(&c->word, comp_word(req_id, status, (uint32_t)(pos >> __builtin_ctz(a.ccap)) + 1u));
 }
 
 // Publishes one reply notification at the next completion position.
 __device__ void write_completion(KArgsC& a, uint64_t req_id, int32_t status,
-                                 const uint8_t* data) {
+                                 const uint64_t* inl) {
   const uint64_t pos = __hip_atomic_fetch_add(&a.dctl->comp_tail, (uint64_t)1,
                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  write_completion_at(a, pos, req_id, status, data);
+  write_completion_at(a, pos, req_id, status, inl);
 }
 
 // Waits until this wave's stores have reached the point where their scope
@@ -250,8 +248,10 @@ __device__ __forceinline__ bool stage_done(KArgsC& a, const Desc& d, bool ring) 
   if (ring && st == CAF_OK && d.hop_actor[0] != 0) return forward_reply(a, slot);
   if (!(d.flags & DF_NO_COMPLETE)) {
     st_dev(&ss->status, 0);
-    const uint8_t* data = (d.flags & DF_INLINE_OUT) ? a.slots[slot].inline_out : nullptr;
-    write_completion(a, d.req_id, st, data);
+    const uint64_t* inl = (d.flags & DF_INLINE_OUT)
+                              ? reinterpret_cast<const uint64_t*>(a.slots[slot].inline_out)
+                              : nullptr;
+    write_completion(a, d.req_id, st, inl);
   }
   return false;
 }
@@ -722,7 +722,7 @@ __device__ void complete_hash_entries(KArgsC& a, DrainLds& L) {
     uint64_t v[2] = {L.hx[i], 0ull};
     // an inline echo replies with its inline input (at most four int32)
     if (L.inl[i]) __builtin_memcpy(v, e.p.raw, sizeof v);
-    write_completion_at(a, L.hpos + j, e.req_id, CAF_OK, reinterpret_cast<const uint8_t*>(v));
+    write_completion_at(a, L.hpos + j, e.req_id, CAF_OK, (e.flags & DF_INLINE_OUT) ? v : nullptr);
   }
 }
 

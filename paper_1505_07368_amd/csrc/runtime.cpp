@@ -469,8 +469,10 @@ void resolve_batch(caf_gpu_system* s, const Comp* recs, uint32_t n) {
   // a duplicate.
   for (uint32_t i = 0; i < n; ++i) {
     const Comp& c = recs[i];
-    const uint32_t slot = (uint32_t)(c.req_id & (kMaxSlots - 1));
-    if (slot >= s->cap || s->slots[slot].req_id != c.req_id) {
+    const uint32_t slot = comp_slot(c.word);
+    constexpr uint64_t seq_mask = (1ull << kCompSeqBits) - 1;
+    if (slot >= s->cap || s->slots[slot].req_id == 0 ||
+        ((s->slots[slot].req_id >> kSlotBits) & seq_mask) != comp_seq(c.word)) {
       s->st_dup++;
       continue;
     }
@@ -492,9 +494,12 @@ void resolve_batch(caf_gpu_system* s, const Comp* recs, uint32_t n) {
   const int64_t t = now_ns();
   for (uint32_t i = 0; i < nf; ++i) {
     caf_future* f = futs[i];
-    f->status = frec[i]->status;
-    if (f->result.on_device == 0 && f->result.data == f->inline_data)
-      std::memcpy(f->inline_data, frec[i]->data, kInlineBytes);
+    f->status = comp_status(frec[i]->word);
+    if (f->result.on_device == 0 && f->result.data == f->inline_data) {
+      // an error record carries no reply bytes
+      if (f->status == CAF_OK) std::memcpy(f->inline_data, frec[i]->data, kInlineBytes);
+      else std::memset(f->inline_data, 0, kInlineBytes);
+    }
     f->t_done = t;
     int expect = 0;
     if (f->state.compare_exchange_strong(expect, 1, std::memory_order_acq_rel)) {
@@ -523,8 +528,10 @@ void poller_main(caf_gpu_system* s) {
     while (n < kPollBatch) {
       const Comp* c = &s->comp[s->comp_head & (ccap - 1)];
       const uint32_t lap = (uint32_t)(s->comp_head / ccap) + 1;
-      if (__atomic_load_n(&c->lap, __ATOMIC_ACQUIRE) != lap) break;
-      std::memcpy(&batch[n], c, sizeof(Comp));
+      const uint64_t word = __atomic_load_n(&c->word, __ATOMIC_ACQUIRE);
+      if (comp_lap(word) != (lap & 0xFFu)) break;
+      batch[n].word = word;
+      std::memcpy(batch[n].data, c->data, kInlineBytes);
       s->comp_head++;
       ++n;
     }
