@@ -72,16 +72,8 @@ __device__ __forceinline__ T ld_sys(const T* p) {
   return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 template <typename T>
-__device__ __forceinline__ T ld_sys_acq(const T* p) {
-  return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-template <typename T>
 __device__ __forceinline__ void st_sys(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-template <typename T>
-__device__ __forceinline__ void st_sys_rel(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 template <typename T>
 __device__ __forceinline__ T ld_dev(const T* p) {
@@ -94,10 +86,6 @@ __device__ __forceinline__ T ld_dev_acq(const T* p) {
 template <typename T>
 __device__ __forceinline__ void st_dev(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ __forceinline__ void st_dev_rel(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <typename T>
 __device__ __forceinline__ bool cas_dev(T* p, T& expected, T desired) {
@@ -118,8 +106,10 @@ __device__ __forceinline__ bool actor_alive(const HostCtl* h, uint32_t actor) {
 // ---- completion -------------------------------------------------------------
 
 // Publishes one reply notification to the host at completion position
-// `pos` (thread-level), after releasing what was written before it.  `inl`:
-// the 16 bytes of a reply that travels inline, else nullptr.
+// `pos` (thread-level).  The message's reply is in memory by now (store_reply,
+// wait_stores and a barrier); what the record itself needs is waited for before
+// the word that makes it valid.  `inl`: the 16 bytes of a reply that travels
+// inline, else nullptr.
 __device__ __forceinline__ void write_completion_at(KArgsC& a, uint64_t pos, uint64_t req_id,
                                                     int32_t status, const uint64_t* inl) {
   Comp* c = &a.comp[pos & (a.ccap - 1u)];  // ccap is a power of two
@@ -127,8 +117,9 @@ __device__ __forceinline__ void write_completion_at(KArgsC& a, uint64_t pos, uin
     uint64_t* dst = reinterpret_cast<uint64_t*>(c->data);
     st_sys(dst, inl[0]);
     st_sys(dst + 1, inl[1]);
+    wait_stores();
   }
-  st_sys_rel(&c->word, comp_word(req_id, status, (uint32_t)(pos >> __builtin_ctz(a.ccap)) + 1u));
+  st_sys(&c->word, comp_word(req_id, status, (uint32_t)(pos >> __builtin_ctz(a.ccap)) + 1u));
 }
 
 // Publishes one reply notification at the next completion position.
@@ -138,10 +129,6 @@ __device__ void write_completion(KArgsC& a, uint64_t req_id, int32_t status,
                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   write_completion_at(a, pos, req_id, status, inl);
 }
-
-// Waits until this wave's stores have reached the point where their scope
-// makes them visible (memory, for the scoped stores above).
-__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Tells the idle workgroups the published count and whether the mailbox holds
 // a backlog (thread-level, drain lock held, after the publication's release).
@@ -196,12 +183,14 @@ constexpr uint32_t kInlineStageTiles = 16;
 
 // Forwards the finished reply in `slot` to the next actor of its pipeline:
 // the slot's descriptor becomes the next stage's (input = this reply).
+// The message's slot is in the workgroup's LDS copy, which is updated.
 // Returns true if the caller's workgroup is to run that stage inline;
 // otherwise the stage is published for any workgroup, or (next actor gone,
 // no room) the request is completed with an error.  Thread-level, drain
 // kernel only.
-CAF_RARE bool forward_reply(KArgsC& a, uint32_t slot) {
-  const Desc d = a.slots[slot].d;
+CAF_RARE bool forward_reply(KArgsC& a, DevSlot& s_slot) {
+  const Desc d = s_slot.d;
+  const uint32_t slot = d.slot;
   const uint32_t hop = d.hop_actor[0];
   const uint32_t actor = (hop & 0xFFFFu) - 1u;
   const uint16_t behavior = (uint16_t)(hop >> 16);
@@ -226,9 +215,10 @@ CAF_RARE bool forward_reply(KArgsC& a, uint32_t slot) {
   nd.p.s.cols = cols;
   nd.flags = (uint16_t)(d.flags & DF_SEND);
   nd.tcfg = 0;
-  a.slots[slot].d = nd;
+  s_slot.d = nd;
   const uint32_t nt = desc_ntiles(nd);
   if (nt <= kInlineStageTiles) return true;
+  a.slots[slot].d = nd;  // released by the publication
   bool ok = lock_drain(a, true);
   if (ok) {
     ok = publish_tiles_locked(a, slot, nt);
@@ -241,55 +231,52 @@ CAF_RARE bool forward_reply(KArgsC& a, uint32_t slot) {
 // Completes (or forwards) the message in `slot` after its current stage:
 // thread 0, once the workgroup's writes of the stage are done.  Returns true
 // if the workgroup is to run the next stage inline.
-__device__ __forceinline__ bool stage_done(KArgsC& a, const Desc& d, bool ring) {
+__device__ __forceinline__ bool stage_done(KArgsC& a, const Desc& d, DevSlot* s_slot) {
   const uint32_t slot = d.slot;
   SlotState* ss = &a.sstate[slot];
   const int32_t st = ld_dev(&ss->status);
-  if (ring && st == CAF_OK && d.hop_actor[0] != 0) return forward_reply(a, slot);
+  if (s_slot && st == CAF_OK && d.hop_actor[0] != 0) return forward_reply(a, *s_slot);
   if (!(d.flags & DF_NO_COMPLETE)) {
     st_dev(&ss->status, 0);
-    const uint64_t* inl = (d.flags & DF_INLINE_OUT)
-                              ? reinterpret_cast<const uint64_t*>(a.slots[slot].inline_out)
-                              : nullptr;
-    write_completion(a, d.req_id, st, inl);
+    uint64_t v[2];
+    if (d.flags & DF_INLINE_OUT)  // written past the caches
+      for (int i = 0; i < 2; ++i)
+        v[i] = ld_dev(reinterpret_cast<const uint64_t*>(a.slots[slot].inline_out) + i);
+    write_completion(a, d.req_id, st, (d.flags & DF_INLINE_OUT) ? v : nullptr);
   }
   return false;
 }
 
-// Accounts `count` finished tiles of message `d` (thread 0, after the
-// workgroup's tile work is complete).  The last tile of a message resets
-// the slot's counters and completes or forwards it; returns true if the
-// workgroup is to run the next pipeline stage inline.  A workgroup that ran
-// every tile of the stage itself (a one-tile message, or a whole GEMM run)
-// skips the shared count: no other workgroup's work has to be waited for.
+// Accounts `count` finished tiles of message `d` (thread 0, after every wave
+// of the workgroup has waited for its stores).  The last tile of a message
+// resets the slot's counters and completes or forwards it; returns true if
+// the workgroup is to run the next pipeline stage inline.  A workgroup that
+// ran every tile of the stage itself (a one-tile message, or a whole GEMM
+// run) skips the shared count: no other workgroup's work has to be waited
+// for.  The ring forms pass the workgroup's LDS copy of the slot.
+//
+// No fence here: the tiles' results are in memory already, so counting them
+// is enough for the record of the last one, and for the host, to find them
+// there.  Only a workgroup that goes on to read results that others wrote
+// drops its caches first.
 __device__ __forceinline__ bool finish_tiles(KArgsC& a, const Desc& d, uint32_t ntiles,
-                                             uint32_t count, bool ring) {
+                                             uint32_t count, DevSlot* s_slot) {
   const uint32_t slot = d.slot;
   SlotState* ss = &a.sstate[slot];
   bool cont = false;
   const bool whole = count == ntiles;
-  // Tiles of a message finished by several workgroups: each releases its
-  // part before counting it (on this chip a release writes back the
-  // workgroup's L2, so it is not free).  A run that finishes the whole
-  // message skips it: what follows -- the completion record (a system-scope
-  // release), a publication of the next stage (an agent-scope release) or
-  // that stage run by this workgroup -- orders the reply's data itself.
-  if (!whole) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
   const uint32_t prev =
       whole ? 0u
             : __hip_atomic_fetch_add(&ss->done, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (prev + count == ntiles) {
-    if (!whole) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (!whole && d.hop_actor[0] != 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     st_dev(&ss->done, 0u);
     st_dev(&ss->decision, 0u);
-    cont = stage_done(a, d, ring);
+    cont = stage_done(a, d, s_slot);
   }
-  if (ring) __hip_atomic_fetch_add(&a.dctl->tiles_done, (uint64_t)count, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+  if (s_slot) __hip_atomic_fetch_add(&a.dctl->tiles_done, (uint64_t)count, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
   return cont;
-}
-__device__ __forceinline__ bool finish_tile(KArgsC& a, const Desc& d, uint32_t ntiles, bool ring) {
-  return finish_tiles(a, d, ntiles, 1u, ring);
 }
 
 // ---- behaviour dispatch -----------------------------------------------------
@@ -308,13 +295,13 @@ __device__ __forceinline__ void hash_step(KArgsC& a, const Desc& d) {
   const uint64_t s = (ld_dev(&act->state) * 1000003ull) ^ d.p.h.x;
   st_dev(&act->state, s);
   uint64_t* io = reinterpret_cast<uint64_t*>(a.slots[d.slot].inline_out);
-  io[0] = s;
-  io[1] = 0;
+  store_reply(io, s);
+  store_reply(io + 1, (uint64_t)0);
   // A reply that does not travel in the completion record goes to the
-  // message's output buffer (a caller-owned one, or the arena's); the
-  // completion that follows releases it.
-  if (!(d.flags & DF_INLINE_OUT) && d.out) *reinterpret_cast<uint64_t*>(d.out) = s;
-  st_dev_rel(&act->seq_done, d.seq + 1u);
+  // message's output buffer (a caller-owned one, or the arena's).
+  if (!(d.flags & DF_INLINE_OUT) && d.out) store_reply(reinterpret_cast<uint64_t*>(d.out), s);
+  wait_stores();  // the state before the number that hands it on
+  st_dev(&act->seq_done, d.seq + 1u);
 }
 
 // LDS of a full variant: the largest work tile, two buffers of a bf16 GEMM
@@ -446,13 +433,14 @@ __device__ __forceinline__ void run_tiles(KArgsC& a, const Desc& d, uint32_t til
 
 // A pipeline stage (row-wise tanh or row sum of a float matrix) run inline
 // by the workgroup that finished the previous stage: every tile in turn.
-// `s_flag` is workgroup-shared scratch.  Whole workgroup.
-__device__ __forceinline__ void run_inline_stages(KArgsC& a, uint32_t slot, uint32_t* s_flag) {
+// `s_slot` holds the stage's descriptor, `s_flag` is workgroup-shared
+// scratch.  Whole workgroup.
+__device__ __forceinline__ void run_inline_stages(KArgsC& a, DevSlot& s_slot, uint32_t* s_flag) {
   for (;;) {
     __syncthreads();
     Desc d;
     {
-      const uint32_t* src = reinterpret_cast<const uint32_t*>(&a.slots[slot].d);
+      const uint32_t* src = reinterpret_cast<const uint32_t*>(&s_slot.d);
       uint32_t* dst = reinterpret_cast<uint32_t*>(&d);
 #pragma unroll
       for (int q = 0; q < (int)(sizeof(Desc) / 4); ++q)
@@ -460,7 +448,7 @@ __device__ __forceinline__ void run_inline_stages(KArgsC& a, uint32_t slot, uint
     }
     const uint32_t nt = desc_ntiles(d);
     for (uint32_t tt = 0; tt < nt; ++tt) {
-      if (ld_dev(&a.sstate[slot].status) == CAF_OK) {
+      if (ld_dev(&a.sstate[d.slot].status) == CAF_OK) {
         if (d.behavior == CAF_BHV_TANH)
           tanh_tile(reinterpret_cast<const float*>(d.in0), reinterpret_cast<float*>(d.out),
                     (uint64_t)d.p.s.rows * d.p.s.cols, tt);
@@ -468,14 +456,13 @@ __device__ __forceinline__ void run_inline_stages(KArgsC& a, uint32_t slot, uint
           rowsum_tile(reinterpret_cast<const float*>(d.in0), reinterpret_cast<float*>(d.out),
                       d.p.s.rows, d.p.s.cols, tt);
         else if (threadIdx.x == 0)
-          st_dev(&a.sstate[slot].status, (int32_t)CAF_E_INVALID);
+          st_dev(&a.sstate[d.slot].status, (int32_t)CAF_E_INVALID);
       }
       __syncthreads();
     }
-    if (threadIdx.x == 0) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      *s_flag = stage_done(a, d, true) ? 1u : 0u;
-    }
+    wait_stores();
+    __syncthreads();
+    if (threadIdx.x == 0) *s_flag = stage_done(a, d, &s_slot) ? 1u : 0u;
     __syncthreads();
     if (!*s_flag) break;
   }
@@ -513,8 +500,9 @@ plain_kernel(KArgs, Desc d, uint32_t ntiles) {
   }
   __syncthreads();
   if (s_dec) run_tiles<kFull>(a, d, blockIdx.x, 1u, smem, &s_ctr);
+  wait_stores();
   __syncthreads();
-  if (threadIdx.x == 0) finish_tile(a, d, ntiles, false);
+  if (threadIdx.x == 0) finish_tiles(a, d, ntiles, 1u, nullptr);
 }
 
 // ---- the mailbox drain ----------------------------------------------------
@@ -697,7 +685,8 @@ __device__ void run_hash_entries_locked(KArgsC& a, DrainLds& L, uint32_t cnt) {
       }
       if (lane == 0 && any) {
         st_dev(&act->state, st);
-        st_dev_rel(&act->seq_done, next);
+        wait_stores();
+        st_dev(&act->seq_done, next);
       }
     }
   }
@@ -731,7 +720,8 @@ __device__ void complete_hash_entries(KArgsC& a, DrainLds& L) {
 __device__ __forceinline__ void retire_launch(KArgsC& a) {
   const uint32_t par = a.gen & 1u;
   for (uint32_t i = 0; i < kBells; ++i) st_dev(&a.dctl->bell[i].leave[par], a.gen);
-  st_sys_rel(&a.hctl->retiring[par], a.gen);
+  wait_stores();
+  st_sys(&a.hctl->retiring[par], a.gen);
 }
 
 // Releases the slots and tile map entries the workgroup wrote: once every
@@ -1094,6 +1084,9 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
   // The claim cursor this workgroup last read: with no more than that
   // published, its bell says so without a look at the counters themselves.
   __shared__ uint64_t s_seen_cur;
+  // Everything published below this is visible to this workgroup: the
+  // published count it had read before its last acquire (thread 0).
+  __shared__ uint64_t s_acq_pub;
   const uint32_t t = threadIdx.x;
   uint64_t last_work = now_ticks();
   // At the start of a launch only the sentinels try the drain lock: every
@@ -1105,6 +1098,7 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
   const auto* bell = &a.dctl->bell[blockIdx.x % kBells];
   if (t == 0) {
     s_seen_cur = 0;
+    s_acq_pub = 0;
     s_seen_drained = ~0ull;
     s_still_since = last_work;
     s_retire_ok = 0;
@@ -1136,6 +1130,7 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
         s_k = (uint32_t)(c.end - c.next);
         c.next = c.end;
         c.own = false;
+        s_acq_pub = c.end;
         cmd = CMD_TILE;
       } else if (c.next < c.end) {
         // the count read while reserving usually covers the new indices; a
@@ -1147,7 +1142,14 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
           s_k = (uint32_t)n;
           c.next += n;
           cmd = CMD_TILE;
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+          // One acquire per publication, not per claim: it empties the CU's
+          // L1 and the XCD's L2, which the other workgroups read their
+          // operands from.  What was published before the last one is
+          // visible already (slots and inputs are complete before that).
+          if (c.next > s_acq_pub) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            s_acq_pub = pub;
+          }
         }
       }
       // Draining an empty mailbox still holds the lock for a host round
@@ -1210,10 +1212,11 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
         // cannot have failed before its tile runs.
         if (ntiles == 1 || s_status == CAF_OK)
           run_tiles<kFull, kBk, kWide>(a, d, tile, run, smem, &s_ctr);
+        wait_stores();
         __syncthreads();
-        if (t == 0) s_cont = finish_tiles(a, d, ntiles, run, true) ? 1u : 0u;
+        if (t == 0) s_cont = finish_tiles(a, d, ntiles, run, &s_slot) ? 1u : 0u;
         __syncthreads();
-        if (s_cont) run_inline_stages(a, d.slot, &s_cont);
+        if (s_cont) run_inline_stages(a, s_slot, &s_cont);
         j += run;
       }
       last_work = now_ticks();
@@ -1289,10 +1292,11 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
   if (t == 0) {
     const uint32_t par = a.gen & 1u;
     const uint32_t prev = __hip_atomic_fetch_add(&a.dctl->wg_exited[par], 1u,
-                                                 __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (prev + 1 == a.grid) {
       st_dev(&a.dctl->wg_exited[par], 0u);
-      st_sys_rel(&a.hctl->exited[par], a.gen);
+      wait_stores();
+      st_sys(&a.hctl->exited[par], a.gen);
     }
   }
 }

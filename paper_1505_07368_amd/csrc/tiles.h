@@ -40,6 +40,22 @@ __device__ __forceinline__ V load_global(const CAF_GLOBAL T* p) {
 }
 __device__ inline uint32_t wave_id() { return threadIdx.x >> 6; }
 
+// Reply data is stored past the L2 (a system-scope store writes through), so
+// a completion needs no writeback of the L2: it waits for the workgroup's
+// stores and writes its record.  A release fence writes back every dirty line
+// of the XCD's L2, whoever wrote it, and holds up its other workgroups
+// meanwhile; with replies left in the L2 each finished message paid one.
+template <typename T>
+__device__ __forceinline__ void store_reply(CAF_GLOBAL T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+template <typename T>
+__device__ __forceinline__ void store_reply(T* p, T v) {
+  store_reply(global_ptr(p), v);
+}
+// Waits until this wave's stores have reached memory.
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // ---------------------------------------------------------------------------
 // Mandelbrot escape time (the paper's Mandelbrot workloads, Sec. 7.4 and
 // Sec. 7.5; the recurrence is the textbook set definition, z_0 = 0,
@@ -181,7 +197,7 @@ __device__ void mandel_tile(const Desc& d, uint32_t tile, uint32_t count, uint32
   }
   const uint32_t width = d.p.m64.width, row0 = d.p.m64.row0, rows = d.p.m64.rows;
   const uint32_t max_iter = d.p.m64.max_iter;
-  uint16_t* out = reinterpret_cast<uint16_t*>(d.out);
+  const auto out = global_ptr(reinterpret_cast<uint16_t*>(d.out));
   // colour reply (a transformation fused at spawn): palette[min(n, len - 1)]
   const bool rgba = (d.flags & DF_RGBA) != 0;
   const auto pal = global_ptr(reinterpret_cast<const uint32_t*>(d.in0));
@@ -236,8 +252,8 @@ __device__ void mandel_tile(const Desc& d, uint32_t tile, uint32_t count, uint32
     for (int k = 0; k < P; ++k) {
       if (!v[k]) continue;
       const uint64_t at = (uint64_t)y[k] * width + x[k];
-      if (rgba) out32[at] = pal[min(n[k], pal_last)];
-      else out[at] = (uint16_t)n[k];
+      if (rgba) store_reply(out32 + at, (uint32_t)pal[min(n[k], pal_last)]);
+      else store_reply(out + at, (uint16_t)n[k]);
     }
   }
   __builtin_amdgcn_s_setprio(0);
@@ -273,7 +289,7 @@ __device__ __forceinline__ void store_c(CAF_GLOBAL float* C, uint32_t n, uint32_
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const uint32_t row = row_base + 8 * (r / 4) + 4 * (lane >> 5) + (r & 3);
-    if (row < n && col < n) C[(uint64_t)row * n + col] = acc[r];
+    if (row < n && col < n) store_reply(C + ((uint64_t)row * n + col), acc[r]);
   }
 }
 
@@ -849,7 +865,7 @@ __device__ void tanh_tile(const float* __restrict__ x, float* __restrict__ y, ui
 #pragma unroll 4
   for (uint32_t e = threadIdx.x; e < kTanhTile; e += kThreads) {
     const uint64_t i = base + e;
-    if (i < count) y[i] = tanhf(x[i]);
+    if (i < count) store_reply(y + i, tanhf(x[i]));
   }
 }
 
@@ -864,7 +880,7 @@ __device__ void rowsum_tile(const float* __restrict__ x, float* __restrict__ y, 
     for (uint32_t c = lane; c < cols; c += 64) s += row[c];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == 0) y[r] = s;
+    if (lane == 0) store_reply(y + r, s);
   }
 }
 
@@ -877,11 +893,12 @@ __device__ void echo_tile(const Desc& d, uint8_t* inline_out) {
     uint32_t w[4];
     __builtin_memcpy(w, d.p.raw, sizeof w);
     const uint32_t i = threadIdx.x;
-    if (i < n) dst[i] = (int32_t)(i == 0 ? w[0] : i == 1 ? w[1] : i == 2 ? w[2] : w[3]);
+    if (i < n)
+      store_reply(dst + i, (int32_t)(i == 0 ? w[0] : i == 1 ? w[1] : i == 2 ? w[2] : w[3]));
     return;
   }
   const int32_t* src = reinterpret_cast<const int32_t*>(d.in0);
-  for (uint32_t i = threadIdx.x; i < n; i += kThreads) dst[i] = src[i];
+  for (uint32_t i = threadIdx.x; i < n; i += kThreads) store_reply(dst + i, src[i]);
 }
 
 }  // namespace cafgpu
