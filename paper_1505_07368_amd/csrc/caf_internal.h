@@ -286,6 +286,10 @@ int cafgpu_request_tagged(caf_gpu_system* sys, caf_actor dst, uint32_t sender, c
                           uint64_t args_bytes, const caf_buf* in, uint32_t n_in,
                           const caf_buf* out_or_null, caf_actor forward_to, caf_future** fut,
                           cafgpu::DriveQ* q, uint32_t tag, bool try_only = false);
+// The driver reads the completion ring itself (between begin and end).
+void cafgpu_help_begin(caf_gpu_system* sys);
+void cafgpu_help_end(caf_gpu_system* sys);
+bool cafgpu_poll_replies(caf_gpu_system* sys);
 bool cafgpu_blocking(const caf_gpu_system* sys);
 int64_t cafgpu_future_issue_ns(const caf_future* f);
 int64_t cafgpu_future_done_ns(const caf_future* f);

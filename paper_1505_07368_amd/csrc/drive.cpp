@@ -23,9 +23,10 @@
 // oldest waiting chain is refused (CAF_E_OVERLOAD) and its reply released.
 // With a non-blocking system, a refused request is final (CAF_E_OVERLOAD).
 //
-// Replies are harvested through a completion queue that the poller thread
-// fills with the tags of resolved requests, so harvesting costs O(1) per
-// reply whatever the window.
+// Replies are harvested through a queue that fills with the tags of resolved
+// requests, so harvesting costs O(1) per reply whatever the window; the
+// driver reads the completion ring itself, so that queue, the futures and the
+// slots stay on its core.
 #include <immintrin.h>
 
 #include <chrono>
@@ -183,6 +184,7 @@ extern "C" int caf_gpu_drive(caf_gpu_system* sys, const caf_msg* msgs, uint64_t 
 
   auto harvest = [&]() -> bool {
     bool any = false;
+    cafgpu_poll_replies(sys);
     const uint64_t tail = __atomic_load_n(&q.tail, __ATOMIC_ACQUIRE);
     while (q.head < tail) {
       const uint32_t k = q.buf[q.head & q.mask];
@@ -193,6 +195,7 @@ extern "C" int caf_gpu_drive(caf_gpu_system* sys, const caf_msg* msgs, uint64_t 
     return any;
   };
 
+  cafgpu_help_begin(sys);
   while (done < count) {
     bool issued = false;
     // chain stages that did not fit go before any new message
@@ -227,6 +230,7 @@ extern "C" int caf_gpu_drive(caf_gpu_system* sys, const caf_msg* msgs, uint64_t 
     }
     if (!harvest() && !issued) _mm_pause();
   }
+  cafgpu_help_end(sys);
   if (elapsed_s) *elapsed_s = (double)(now_ns() - t_start) * 1e-9;
   return first_err;
 }

@@ -757,7 +757,7 @@ __device__ __forceinline__ bool drain_once_body(KArgsC& a, DrainLds& L, bool may
   if (t == 0) L.any_echo = 0;
   if (t == 0) L.nbig = 0;
   if (t == 0) {
-    // All six loads are in flight together; one system-scope acquire fence
+    // All seven loads are in flight together; one system-scope acquire fence
     // after them orders the entry reads below after the tail (each acquire
     // load on its own would wait for its own round trip).  A look at an empty
     // mailbox has nothing to order, and the fence would empty the L2 that the
@@ -768,13 +768,18 @@ __device__ __forceinline__ bool drain_once_body(KArgsC& a, DrainLds& L, bool may
     const uint64_t pubv = ld_dev(&a.dctl->tiles_pub);
     const uint64_t done = ld_dev(&a.dctl->tiles_done);
     const uint32_t had_backlog = ld_dev(&a.dctl->backlog);
-    const uint64_t avail = tail - d;
+    const uint32_t leave = ld_dev(&a.dctl->bell[0].leave[a.gen & 1u]);
+    // A launch that retires takes no more messages: its workgroups are
+    // leaving, and the few that are not out yet would run everything that the
+    // message brings (a 776-tile image took 21 ms so).  The host sees the
+    // messages waiting and starts the next launch.
+    const uint64_t avail = leave == a.gen ? 0 : tail - d;
     if (avail) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
     L.d = d;
     L.cnt = avail < a.max_batch ? avail : a.max_batch;
     // Lets idle workgroups help while a backlog remains (relaxed: a hint).
     L.backlog = avail > a.max_batch ? 1u : 0u;
-    if (had_backlog != L.backlog) {
+    if (had_backlog != L.backlog && leave != a.gen) {
       st_dev(&a.dctl->backlog, L.backlog);
       ring_bells(a, pubv, L.backlog);
     }
