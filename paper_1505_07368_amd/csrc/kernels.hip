@@ -414,8 +414,9 @@ __device__ __forceinline__ void run_tiles(KArgsC& a, const Desc& d, uint32_t til
       } else {
         const float* A = reinterpret_cast<const float*>(d.in0);
         const float* B = reinterpret_cast<const float*>(d.in1);
-        if (d.tcfg == 128) gemm_f32_tile<128>(A, B, C, d.p.g.n, tile, count, (float*)smem);
-        else gemm_f32_tile<64>(A, B, C, d.p.g.n, tile, count, (float*)smem);
+        constexpr int kNBuf = kBk == kBf16SliceK ? 2 : 1;  // the LDS of this variant
+        if (d.tcfg == 128) gemm_f32_tile<128, kNBuf>(A, B, C, d.p.g.n, tile, count, (float*)smem);
+        else gemm_f32_tile<64, kNBuf>(A, B, C, d.p.g.n, tile, count, (float*)smem);
       }
       return;
     }

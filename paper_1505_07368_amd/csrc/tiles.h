@@ -293,152 +293,365 @@ __device__ __forceinline__ void store_c(CAF_GLOBAL float* C, uint32_t n, uint32_
   }
 }
 
-// Per-thread register staging of one K slice: the next slice is loaded from
-// global memory while the matrix cores work on the current one (from the
-// other LDS buffer), so one barrier per slice suffices.
+// fp32 inputs, on the bf16 matrix cores.  Each operand element is split into
+// three bf16 terms, a = a1 + a2 + a3: a1 = bf16(a), a2 = bf16(a - a1),
+// a3 = a - a1 - a2, which is exact (3 x 8 significant bits and the signs hold
+// fp32's 24), and a product is the six terms a1 b1, a1 b2, a2 b1, a2 b2,
+// a1 b3, a3 b1, each exact in fp32 and accumulated there (of the three left
+// out, a2 b3 and a3 b2 have a root mean square of 2^-26 of |a b|).  Six
+// 32x32x16 bf16 instructions (32 cycles each) replace eight 32x32x2 fp32 ones
+// (64 cycles each).  Against float64 the sums are no further off than the
+// fp32 instructions': they are rounded six times per 16 k instead of eight
+// times (relative error for entries U(-1, 1), fp32 instructions / split:
+// n = 64 1.4e-7 / 1.1e-7, 512 4.0e-7 / 3.4e-7, 1024 5.7e-7 / 4.8e-7).
+// Products in a batch, 1024 of n = 512: 3277 -> 2167 us (84 -> 127 TFLOP/s),
+// n = 4096: 109 -> 166; the clock drops to 1.7 GHz under this load, and the
+// rate of the bf16 instructions there, a sixth of 1.3 PFLOP/s, bounds it.
+//
+// The split is exact only while no term underflows, and a value near the top
+// of the range rounds to infinity.  So a tile is redone with the fp32
+// instructions (gemm_f32_direct) if the smallest non-zero magnitudes of its A
+// rows and B columns are below 2^-103, or their product below 2^-100, or if
+// an output is not finite: infinities, NaNs, tiny and huge inputs come out as
+// those instructions give them.
+//
+// Layout.  K advances in slices of 16 (TE = 128) or 2 x 16 (TE = 64), which
+// two waves load as A and two as B, 16 elements per thread.  LDS holds, per
+// 16 deep sub-slice, the three terms of A as [row][k] and of B as
+// [column][k], rows of 32 bytes padded to 48 (16-byte reads of 8 consecutive
+// rows touch distinct banks); two terms of consecutive k are packed by one
+// conversion, which also transposes B.  Registers hold the next two slices,
+// so a load has two slices of matrix work to arrive in.
+//
+// Any n >= 4 and any alignment of floats: 16-byte loads, from addresses
+// clamped into the matrix, put right in the last slice of a tile where n is
+// no multiple of the slice depth (512 products of n = 17 .. 500: 1316 ->
+// 486 us; element loads before).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-// fp32 inputs: v_mfma_f32_32x32x2f32, k slices of 16; LDS A k-major
-// (transposed on store), B row-major.  smem: 2 x 2 x 16 x TE floats.  One
-// call computes `count` consecutive output tiles (row-major tile order) of
-// one product, as one stream of slices like the bf16 tile below.
-template <int TE>
-__device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A, const float* __restrict__ B,
-                              float* __restrict__ C, uint32_t n, uint32_t tile0,
-                              uint32_t count, float* smem) {
-  constexpr int BK = 16;
-  constexpr int WB = TE / 64;               // 32x32 blocks per wave and dimension
-  constexpr int Q = TE * BK / 4 / kThreads; // float4 per thread and operand
-  constexpr int SLICE = 2 * BK * TE;        // floats per LDS buffer
+// One 32 x 32 block of C by one wave with the fp32 matrix instructions,
+// operands straight from memory: n < 4 and the tiles described above.
+__device__ __noinline__ void gemm_f32_direct(const float* A, const float* B, float* C, uint32_t n,
+                                             uint32_t row0, uint32_t col0) {
   const auto Ag = global_ptr(A);
   const auto Bg = global_ptr(B);
+  const uint32_t lane = lane_id(), kl = lane >> 5;
+  const uint32_t row = min(row0 + (lane & 31), n - 1u), col = min(col0 + (lane & 31), n - 1u);
+  floatx16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  for (uint32_t k0 = 0; k0 < n; k0 += 16) {
+    float a[8], b[8];
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q) {
+      const uint32_t k = k0 + 2 * q + kl, kc = min(k, n - 1u);
+      a[q] = Ag[(uint64_t)row * n + kc];
+      b[q] = Bg[(uint64_t)kc * n + col];
+      if (k >= n) a[q] = b[q] = 0.f;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], acc, 0, 0, 0);
+  }
+  store_c<32>(global_ptr(C), n, row0, col0, acc);
+}
+
+// The exponents (biased) below which a tile's split may lose bits.
+constexpr uint32_t kSplitMinExp = 127 - 103;
+constexpr uint32_t kSplitMinExpSum = 2 * 127 - 100;
+
+// The part of a tile stream that one wave runs: the waves that load A and
+// those that load B differ in how they split and store a slice, and each has
+// its own copy of the loop, so that a step is one basic block in which the
+// split's vector instructions are scheduled between the matrix instructions
+// (a 32-cycle matrix instruction leaves seven vector issue slots).
+template <int TE, int NBUF, bool kA>
+__device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
+                                                const float* __restrict__ B,
+                                                float* __restrict__ C, uint32_t n, uint32_t tile0,
+                                                uint32_t count, uint8_t* lds,
+                                                uint32_t (*s_min)[2]) {
+  constexpr uint32_t WB = TE / 64;           // 32 x 32 blocks per wave and dimension
+  constexpr uint32_t SUB = 128 / TE;         // 16 deep sub-slices per slice
+  constexpr uint32_t KS = 16 * SUB;          // k per slice
+  constexpr uint32_t ROW = 48;               // bytes of an LDS row
+  constexpr uint32_t PLANE = TE * ROW;       // one term of one operand, one sub-slice
+  constexpr uint32_t OPND = 3 * PLANE;       // its three terms
+  constexpr uint32_t BUF = SUB * 2 * OPND;   // bytes of an LDS buffer
+  static_assert(BUF == 36864, "slice buffer");
   const auto Cg = global_ptr(C);
+  const auto src = reinterpret_cast<const CAF_GLOBAL uint8_t*>(global_ptr(kA ? A : B));
   const uint32_t t = threadIdx.x, lane = lane_id(), w = wave_id();
   const uint32_t wm = w >> 1, wn = w & 1;
-  const bool vec = (n % 4u) == 0 && ((reinterpret_cast<uintptr_t>(A) |
-                                      reinterpret_cast<uintptr_t>(B)) & 15u) == 0;
+  const uint32_t tt = t & 127u;
+
   floatx16 acc[WB][WB];
   auto zero_acc = [&]() {
 #pragma unroll
-    for (int i = 0; i < WB; ++i)
+    for (uint32_t i = 0; i < WB; ++i)
 #pragma unroll
-      for (int j = 0; j < WB; ++j)
+      for (uint32_t j = 0; j < WB; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
   };
-  auto store_tile = [&](uint32_t tm, uint32_t tn) {
-#pragma unroll
-    for (int i = 0; i < WB; ++i)
-#pragma unroll
-      for (int j = 0; j < WB; ++j)
-        store_c<TE>(Cg, n, tm * TE + wm * (TE / 2) + i * 32, tn * TE + wn * (TE / 2) + j * 32,
-                    acc[i][j]);
-  };
-  auto mfma_slice = [&](const float* As, const float* Bs) {
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      const uint32_t kr = kk + (lane >> 5);
-      float a[WB], b[WB];
-#pragma unroll
-      for (int i = 0; i < WB; ++i) a[i] = As[kr * TE + wm * (TE / 2) + i * 32 + (lane & 31)];
-#pragma unroll
-      for (int j = 0; j < WB; ++j) b[j] = Bs[kr * TE + wn * (TE / 2) + j * 32 + (lane & 31)];
-#pragma unroll
-      for (int i = 0; i < WB; ++i)
-#pragma unroll
-        for (int j = 0; j < WB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-  };
   zero_acc();
 
-  if (vec) {
-    // Per-lane zero fill at the edges: a load outside the matrix is not
-    // issued and its registers hold zeros.
-    float4 ra[Q], rb[Q];
-    auto gload = [&](uint32_t tm, uint32_t tn, uint32_t k0) {
+  const uint32_t nk = (n + KS - 1) / KS;  // slices per tile
+  const uint32_t steps = count * nk;
+  // What a thread loads of a slice.  A: four rows TE / 4 apart, 4 k each (the
+  // lanes of a row side by side).  B: a block of 4 k x 4 columns.
+  const uint32_t a_row = tt / (4 * SUB), a_k = (tt % (4 * SUB)) * 4;
+  const uint32_t b_k = (tt & 3u) * 4 + (tt / TE) * 16, b_col = ((tt % TE) >> 2) * 4;
+  // Element offsets of its four 16-byte loads, clamped to the matrix's last
+  // four elements: a load past the end of a row reads the next row's first
+  // elements, one past the matrix its last ones.  Rows and columns beyond n
+  // only feed outputs that are not stored; k beyond n is put right by fix().
+  const uint32_t last4 = n * n - 4u;
+  const uint32_t stride = kA ? (TE / 4) * n : n;  // between the four loads
+  const uint32_t kstep = kA ? KS : KS * n;        // between slices
+  struct Slice {
+    f32x4u v[4];
+  };
+  uint32_t ltile = tile0, lk = 0, loff;  // the slice to load next
+  auto seek = [&]() {
+    uint32_t tm, tn;
+    tile_coords(ltile, n, TE, tm, tn);
+    loff = kA ? (tm * TE + a_row) * n + a_k : b_k * n + tn * TE + b_col;
+  };
+  seek();
+  auto load = [&](Slice& s) {
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const uint32_t idx = t + kThreads * q;
-        const uint32_t row = idx / (BK / 4), kq = (idx % (BK / 4)) * 4;
-        const uint32_t gr = tm * TE + row, gk = k0 + kq;
-        ra[q] = (gr < n && gk < n) ? load_global<float4>(Ag + (uint64_t)gr * n + gk)
-                                   : make_float4(0.f, 0.f, 0.f, 0.f);
-        const uint32_t kr = idx / (TE / 4), c = (idx % (TE / 4)) * 4;
-        const uint32_t gk2 = k0 + kr, gc = tn * TE + c;
-        rb[q] = (gk2 < n && gc < n) ? load_global<float4>(Bg + (uint64_t)gk2 * n + gc)
-                                    : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-    };
-    auto lstore = [&](float* buf) {
-      float* As = buf;
-      float* Bs = buf + BK * TE;
+    for (uint32_t q = 0; q < 4; ++q) {
+      const uint32_t off = min(loff + q * stride, last4) * 4u;
+      s.v[q] = *reinterpret_cast<const CAF_GLOBAL f32x4u*>(src + off);
+    }
+  };
+  auto load_next = [&](uint32_t step) {  // advances to slice `step` (at most one further)
+    if (step >= steps) return;
+    if (++lk == nk) {
+      lk = 0;
+      ++ltile;
+      seek();
+    } else {
+      loff += kstep;
+    }
+  };
+  // elements d .. 3 of v moved to the front, zeros behind (d >= 4: all zeros)
+  auto shift = [](f32x4u v, uint32_t d) {
+    f32x4u r;
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const uint32_t idx = t + kThreads * q;
-        const uint32_t row = idx / (BK / 4), kq = (idx % (BK / 4)) * 4;
-        As[(kq + 0) * TE + row] = ra[q].x;
-        As[(kq + 1) * TE + row] = ra[q].y;
-        As[(kq + 2) * TE + row] = ra[q].z;
-        As[(kq + 3) * TE + row] = ra[q].w;
-        const uint32_t kr = idx / (TE / 4), c = (idx % (TE / 4)) * 4;
-        *reinterpret_cast<float4*>(Bs + kr * TE + c) = rb[q];
-      }
-    };
-    const uint32_t nk = (n + BK - 1) / BK;  // slices per tile
-    const uint32_t steps = count * nk;
-    uint32_t tile = tile0, k = 0, tm, tn;
-    tile_coords(tile, n, TE, tm, tn);
-    gload(tm, tn, 0);
-    lstore(smem);
-    __syncthreads();
-    uint32_t cur = 0;
-    for (uint32_t s = 0; s + 1 < steps; ++s) {
-      const bool tile_ends = k + 1 == nk;
-      const uint32_t otm = tm, otn = tn;
-      const uint32_t k1 = tile_ends ? 0u : k + 1;
-      if (tile_ends) tile_coords(tile + 1, n, TE, tm, tn);
-      gload(tm, tn, k1 * BK);
-      const float* buf = smem + cur * SLICE;
-      mfma_slice(buf, buf + BK * TE);
-      if (tile_ends) {
-        store_tile(otm, otn);
-        zero_acc();
-        ++tile;
-      }
-      lstore(smem + (cur ^ 1u) * SLICE);
-      __syncthreads();
-      cur ^= 1u;
-      k = k1;
+    for (int e = 0; e < 4; ++e) {
+      float x = d == 0 ? v[e] : 0.f;
+#pragma unroll
+      for (int f = e + 1; f < 4; ++f) x = d == (uint32_t)(f - e) ? v[f] : x;
+      r[e] = x;
     }
-    {
-      const float* buf = smem + cur * SLICE;
-      mfma_slice(buf, buf + BK * TE);
-      store_tile(tm, tn);
+    return r;
+  };
+  // The last slice of a tile where n is no multiple of KS: loads that were
+  // clamped are moved back into place, and k beyond n is zero in A and in B
+  // (in both: the other operand's leftovers may be infinite).
+  auto fix = [&](Slice& s, uint32_t tm, uint32_t tn) {
+    const uint32_t k0 = (nk - 1) * KS;
+    const uint32_t off = kA ? (tm * TE + a_row) * n + k0 + a_k : (k0 + b_k) * n + tn * TE + b_col;
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      const uint32_t o = off + q * stride;
+      const uint32_t d = o - min(o, last4);
+      s.v[q] = shift(s.v[q], d);
+      if constexpr (kA) {
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e)
+          if (k0 + a_k + e >= n) s.v[q][e] = 0.f;
+      } else {
+        if (k0 + b_k + q >= n) s.v[q] = f32x4u{0.f, 0.f, 0.f, 0.f};
+      }
     }
-  } else {
-    // ragged or unaligned operands: element loads, one buffer, tile by tile
-    float* As = smem;
-    float* Bs = smem + BK * TE;
-    for (uint32_t i = 0; i < count; ++i) {
-      uint32_t tm, tn;
-      tile_coords(tile0 + i, n, TE, tm, tn);
-      if (i) zero_acc();
-      for (uint32_t k0 = 0; k0 < n; k0 += BK) {
-        for (uint32_t idx = t; idx < (uint32_t)(TE * BK); idx += kThreads) {
-          const uint32_t row = idx / BK, kk = idx % BK;
-          const uint32_t gr = tm * TE + row, gk = k0 + kk;
-          As[kk * TE + row] = (gr < n && gk < n) ? Ag[(uint64_t)gr * n + gk] : 0.f;
-          const uint32_t kr = idx / TE, c = idx % TE;
-          const uint32_t gk2 = k0 + kr, gc = tn * TE + c;
-          Bs[kr * TE + c] = (gk2 < n && gc < n) ? Bg[(uint64_t)gk2 * n + gc] : 0.f;
+  };
+  uint32_t vmin = 0xFFFFFFFFu;  // smallest (bits << 1) - 1 of this thread's elements of the tile
+  auto seen = [&](float x) { return (__builtin_bit_cast(uint32_t, x) << 1) - 1u; };
+  // two consecutive k of one row or column -> a packed pair of each term
+  auto split = [&](float x, float y, uint32_t (&p)[3]) {
+    vmin = min(vmin, min(seen(x), seen(y)));
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const f32x2 xy = {x, y};
+      const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(xy, bf16x2));
+      p[q] = h;
+      if (q < 2) {
+        x = x - __builtin_bit_cast(float, h << 16);
+        y = y - __builtin_bit_cast(float, h & 0xFFFF0000u);
+      }
+    }
+  };
+  const uint32_t dst0 = kA ? (a_k >> 4) * (2 * OPND) + a_row * ROW + (a_k & 15u) * 2
+                           : (b_k >> 4) * (2 * OPND) + OPND + b_col * ROW + (b_k & 15u) * 2;
+  auto lstore = [&](const Slice& s, uint8_t* buf) {
+    uint8_t* dst = buf + dst0;
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {  // row q of A, column q of B
+      uint32_t lo[3], hi[3];
+      split(kA ? s.v[q][0] : s.v[0][q], kA ? s.v[q][1] : s.v[1][q], lo);
+      split(kA ? s.v[q][2] : s.v[2][q], kA ? s.v[q][3] : s.v[3][q], hi);
+#pragma unroll
+      for (uint32_t p = 0; p < 3; ++p)
+        *reinterpret_cast<uint2*>(dst + p * PLANE + q * (kA ? TE / 4 : 1) * ROW) =
+            make_uint2(lo[p], hi[p]);
+    }
+  };
+  auto note_min = [&](uint32_t tseq) {  // the tile's last slice is in LDS
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) vmin = min(vmin, (uint32_t)__shfl_xor((int)vmin, off));
+    if (lane == 0) atomicMin(&s_min[tseq % 3][kA ? 0 : 1], vmin);
+    vmin = 0xFFFFFFFFu;
+  };
+  auto mfma_slice = [&](const uint8_t* buf) {
+#pragma unroll
+    for (uint32_t sub = 0; sub < SUB; ++sub) {
+      const uint8_t* As = buf + sub * (2 * OPND) + (lane >> 5) * 16;
+      const uint8_t* Bs = As + OPND;
+      bf16x8 a[3][WB], b[3][WB];
+#pragma unroll
+      for (uint32_t p = 0; p < 3; ++p)
+#pragma unroll
+        for (uint32_t i = 0; i < WB; ++i) {
+          a[p][i] = __builtin_bit_cast(
+              bf16x8, *reinterpret_cast<const uint4*>(
+                          As + p * PLANE + (wm * (TE / 2) + i * 32 + (lane & 31)) * ROW));
+          b[p][i] = __builtin_bit_cast(
+              bf16x8, *reinterpret_cast<const uint4*>(
+                          Bs + p * PLANE + (wn * (TE / 2) + i * 32 + (lane & 31)) * ROW));
         }
-        __syncthreads();
-        mfma_slice(As, Bs);
-        __syncthreads();
-      }
-      store_tile(tm, tn);
+      // the small terms first
+      constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (uint32_t i = 0; i < WB; ++i)
+#pragma unroll
+          for (uint32_t j = 0; j < WB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]][i], b[PB[q]][j],
+                                                                acc[i][j], 0, 0, 0);
     }
+  };
+  // Stores the tile, or has it redone where the split does not hold.
+  auto finish_tile = [&](uint32_t tm, uint32_t tn, uint32_t tseq) {
+    const uint32_t ma = s_min[tseq % 3][0], mb = s_min[tseq % 3][1];
+    const uint32_t ea = (ma + 1u) >> 24, eb = (mb + 1u) >> 24;
+    // an operand of zeros only (0xFFFFFFFF) is exact
+    bool redo = ma != 0xFFFFFFFFu && mb != 0xFFFFFFFFu &&
+                (ea < kSplitMinExp || eb < kSplitMinExp || ea + eb < kSplitMinExpSum);
+    float big[4] = {0.f, 0.f, 0.f, 0.f};  // NaN if an output is not finite
+#pragma unroll
+    for (uint32_t i = 0; i < WB; ++i)
+#pragma unroll
+      for (uint32_t j = 0; j < WB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) big[r & 3] = __builtin_fmaf(acc[i][j][r], 0.f, big[r & 3]);
+    const float any = (big[0] + big[1]) + (big[2] + big[3]);
+    redo = __builtin_amdgcn_ballot_w64(redo || !(any == 0.f)) != 0;
+    const uint32_t r0 = tm * TE + wm * (TE / 2), c0 = tn * TE + wn * (TE / 2);
+    if (__builtin_expect(redo, 0)) {
+      for (uint32_t i = 0; i < WB; ++i)
+        for (uint32_t j = 0; j < WB; ++j)
+          if (r0 + i * 32 < n && c0 + j * 32 < n)
+            gemm_f32_direct(A, B, C, n, r0 + i * 32, c0 + j * 32);
+    } else {
+#pragma unroll
+      for (uint32_t i = 0; i < WB; ++i)
+#pragma unroll
+        for (uint32_t j = 0; j < WB; ++j)
+          store_c<TE>(Cg, n, r0 + i * 32, c0 + j * 32, acc[i][j]);
+    }
+    zero_acc();
+    if (t < 2) s_min[(tseq + 2) % 3][t] = 0xFFFFFFFFu;
+  };
+
+  Slice s0, s1;
+  const bool ragged = n % KS != 0;
+  // the slice that goes to LDS next: its position and its tile
+  uint32_t sk = 0, sseq = 0, stm, stn;
+  tile_coords(tile0, n, TE, stm, stn);
+  load(s0);
+  load_next(1);
+  load(s1);  // with a single slice, that slice again
+  load_next(2);
+  if (ragged && nk == 1) fix(s0, stm, stn);
+  lstore(s0, lds);
+  if (nk == 1) note_min(0);
+  __syncthreads();
+  uint32_t ctm = stm, ctn = stn, ck = 0, cseq = 0;  // the slice computed
+  // Computes slice s from LDS, loads slice s + 2 into `in` and puts slice
+  // s + 1, `out`, into LDS.  Past the end it loads and stores the last slice
+  // again, into a buffer nobody reads.
+  auto step = [&](uint32_t s, Slice& in, Slice& out) {
+    const bool more = s + 1 < steps;
+    if (more && ++sk == nk) {
+      sk = 0;
+      ++sseq;
+      tile_coords(tile0 + sseq, n, TE, stm, stn);
+    }
+    if (ragged && sk == nk - 1 && more) fix(out, stm, stn);
+    load(in);
+    load_next(s + 3);
+    __builtin_amdgcn_sched_barrier(0);
+    mfma_slice(lds + (NBUF == 2 ? (s & 1u) * BUF : 0u));
+    if constexpr (NBUF == 1) __syncthreads();  // every wave has read the buffer
+    lstore(out, lds + (NBUF == 2 ? ((s + 1) & 1u) * BUF : 0u));
+    if constexpr (NBUF == 2) {
+      // matrix instructions with the split between them
+      __builtin_amdgcn_sched_group_barrier(0x100, 4 * WB, 0);  // fragments first
+#pragma unroll
+      for (uint32_t q = 0; q < 6 * SUB * WB * WB; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
+        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (sk == nk - 1 && more) note_min(sseq);
+    if (ck == nk - 1) {
+      finish_tile(ctm, ctn, cseq);
+      ++cseq;
+      ck = 0;
+    } else {
+      ++ck;
+    }
+    ctm = stm;
+    ctn = stn;
+    __syncthreads();
+  };
+  for (uint32_t s = 0; s < steps; s += 2) {
+    step(s, s0, s1);
+    if (s + 1 < steps) step(s + 1, s1, s0);
   }
+}
+
+// NBUF: LDS buffers (2, or 1 where the kernel variant has half the LDS).
+// One call computes `count` consecutive output tiles (row-major tile order)
+// of one product, as one stream of slices.  smem: NBUF x 36 KB.
+template <int TE, int NBUF = 2>
+__device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A,
+                                              const float* __restrict__ B,
+                                              float* __restrict__ C, uint32_t n, uint32_t tile0,
+                                              uint32_t count, float* smem) {
+  // smallest non-zero magnitude of the tile's A and B, as (bits << 1) - 1;
+  // three tiles in turn, so that one is cleared while the next is in use
+  __shared__ uint32_t s_min[3][2];
+  const uint32_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(wave_id());
+  uint8_t* lds = reinterpret_cast<uint8_t*>(smem);
+  if (n < 4) {  // one tile
+    if (w == 0) gemm_f32_direct(A, B, C, n, 0, 0);
+    __syncthreads();
+    return;
+  }
+  if (t < 6) s_min[t >> 1][t & 1u] = 0xFFFFFFFFu;
+  __syncthreads();
+  if (w < 2) gemm_f32_stream<TE, NBUF, true>(A, B, C, n, tile0, count, lds, s_min);
+  else gemm_f32_stream<TE, NBUF, false>(A, B, C, n, tile0, count, lds, s_min);
 }
 
 // bfloat16 inputs: v_mfma_f32_32x32x16_bf16, k slices of kBf16SliceK.  Both operands
