@@ -142,7 +142,8 @@ typedef struct {
                               aligned inputs; the others get 128 or their class's
                               edge */
   uint32_t gemm_tile_class[4]; /* the same choice for n <= 64, <= 128, <= 256, > 256;
-                                  0 = default (64 up to n = 128, else 128) */
+                                  0 = default (64 up to n = 64, else 128; fp32 products
+                                  64 while the chip has room for more tiles) */
   uint32_t full_wgs_per_cu; /* drain workgroups per compute unit while a GEMM actor
                                exists: 0 or 2 = two (64-deep bf16 slices; suits
                                matrix-heavy loads), 3 = three (32-deep bf16

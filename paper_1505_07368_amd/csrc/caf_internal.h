@@ -210,8 +210,7 @@ __host__ __device__ inline uint32_t mandel_blocks(uint32_t width, uint32_t rows,
 // A product's output tiles (tcfg x tcfg blocks of C) and the work units
 // they are claimed and completed in: `unit` consecutive tiles in row-major
 // tile order.  A unit that covers a whole product completes it without the
-// shared tile count and the release before it; units of several tiles
-// therefore suit products whose tiles are short next to that release.
+// shared tile count.
 // tcfg 64 or 128: square tiles of that edge; 256: 128 x 256 tiles (bf16).
 __host__ __device__ inline uint32_t gemm_tiles(const Desc& d) {
   if (d.tcfg == 256) return ((d.p.g.n + 127) / 128) * ((d.p.g.n + 255) / 256);
@@ -219,12 +218,6 @@ __host__ __device__ inline uint32_t gemm_tiles(const Desc& d) {
   return t * t;
 }
 __host__ __device__ inline uint32_t gemm_unit(const Desc& d) { return d.p.g.unit ? d.p.g.unit : 1u; }
-// bf16 products: four tiles per unit.  A 128 x 128 bf16 tile is short next
-// to the agent-scope release (an L2 writeback) that a partial run needs, so
-// a product of up to four tiles completes whole; fp32 tiles are long
-// enough that single tiles end a batch more evenly.
-constexpr uint32_t kGemmUnitBf16 = 4;
-
 // Claimable work units of a message (the drain's "tiles").
 __host__ __device__ inline uint32_t desc_ntiles(const Desc& d) {
   switch (d.behavior) {

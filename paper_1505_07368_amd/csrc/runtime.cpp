@@ -659,7 +659,17 @@ int check_signature(const ActorRec& a, const void* args, uint64_t args_bytes, co
 // are staged into the arena, which is) -- whatever its size class asks for:
 // in that variant the square tiles are calls.  Other products get their
 // class's edge, 128 where that is 256.
-uint32_t gemm_tile_for(const caf_gpu_system* s, const caf_gemm_args* g, const caf_buf* in) {
+//
+// Without a choice by the caller, the edge follows the load: `ahead` messages
+// are out and not answered.  An fp32 product alone, or with the 128-tiles of
+// all of them filling less than an eighth of the grid (the first of a burst
+// would be cut small otherwise), is cut into 64-tiles (one product alone:
+// n = 256 28 against 36 us, 1024 69 against 116, 1536 132 against 170; at
+// 2048 193 against 208, but two at once 315 against 237); with the chip busy 128 is better from n = 65 on
+// (1,024 products of 128: 168 against 256 us).  bf16 tiles are short: 128
+// always.  The edge does not change the sums.
+uint32_t gemm_tile_for(const caf_gpu_system* s, const caf_gemm_args* g, const caf_buf* in,
+                       uint64_t ahead) {
   const uint32_t n = g->n;
   if (s->kargs.wide && g->in_dtype == CAF_BF16 && n % 32 == 0) {
     bool aligned = true;
@@ -671,9 +681,27 @@ uint32_t gemm_tile_for(const caf_gpu_system* s, const caf_gemm_args* g, const ca
   if (t == 0) {
     const uint32_t cls = n <= 64 ? 0u : n <= 128 ? 1u : n <= 256 ? 2u : 3u;
     t = s->cfg.gemm_tile_class[cls];
-    if (t == 0) t = n <= 128 ? 64u : 128u;
+    if (t == 0) {
+      const uint64_t e = (n + 127) / 128;
+      const bool idle = (ahead + 1) * e * e < s->grid_full / (ahead ? 8 : 3);
+      t = n <= 64 || (g->in_dtype == CAF_F32 && idle) ? 64u : 128u;
+    }
   }
   return t == 256 ? 128u : t;
+}
+
+// Output tiles per work unit of a product of `tiles` tiles.  A product that
+// one workgroup completes needs no shared count and its tiles run as one
+// stream of slices: four tiles per unit up to four tiles, two up to sixteen
+// (1,024 products of n = 256: fp32 402 -> 353 us, bf16 301 -> 218; 148 bf16
+// products of 512: 224 -> 179; larger ones gain nothing, and a single large
+// product would leave workgroups idle: n = 4096 in bf16 350 us in units of
+// four, 241 in single tiles).  Smaller while the units of all products
+// together do not fill an eighth of the grid.
+uint32_t gemm_unit_for(const caf_gpu_system* s, uint32_t tiles, uint64_t ahead) {
+  uint32_t u = tiles <= 4 ? 4u : tiles <= 16 ? 2u : 1u;
+  while (u > 1 && (ahead + 1) * ((tiles + u - 1) / u) < s->grid_full / 8) u /= 2;
+  return u;
 }
 
 // Builds the descriptor of the first stage (all fields except slot, seq and
@@ -715,12 +743,10 @@ void fill_desc(const caf_gpu_system* s, const ActorRec& a, uint32_t aidx, const 
       const caf_gemm_args* g = (const caf_gemm_args*)args;
       if (g->in_dtype == CAF_BF16) d->flags |= DF_BF16;
       d->p.g.n = g->n;
-      d->tcfg = gemm_tile_for(s, g, in);
-      // bf16 products in units of four tiles, 128 x 256 ones too (half of an
-      // n = 512 product; with drained products in mailbox order four ran a
-      // batch 1.5-3% faster than two and 7% faster than eight, whose units
-      // are too coarse to end a batch evenly); fp32 in single tiles
-      d->p.g.unit = g->in_dtype != CAF_BF16 ? 1u : kGemmUnitBf16;
+      // the messages ahead of this one; a launch per message has the chip to itself
+      const uint64_t ahead = s->plain() ? 0 : s->outstanding.load(std::memory_order_relaxed);
+      d->tcfg = gemm_tile_for(s, g, in, ahead);
+      d->p.g.unit = gemm_unit_for(s, gemm_tiles(*d), ahead);
       break;
     }
     case CAF_BHV_TANH:
