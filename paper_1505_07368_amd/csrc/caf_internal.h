@@ -188,7 +188,6 @@ struct KArgs {
   uint32_t grid;
   uint32_t full;          // drain launch variant: 1 = every behaviour, 0 = all but GEMM
   uint32_t full_wgs;      // workgroups per compute unit of the full variant (2 or 3)
-  uint32_t wide;          // full launches use the variant with 128 x 256 bf16 tiles
 };
 
 // ---- work-tile geometry (host and device agree on it) -------------------

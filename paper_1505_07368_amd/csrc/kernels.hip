@@ -305,24 +305,29 @@ __device__ __forceinline__ void hash_step(KArgsC& a, const Desc& d) {
 }
 
 // LDS of a full variant: the largest work tile, two buffers of a bf16 GEMM
-// slice at TE = 128, for slices of bk (with 64-deep slices it also holds the
-// three stages of a wide bf16 tile).  The light variant only needs the drain
-// scratch.
-constexpr uint32_t smem_bytes(int bk) { return 2 * (2 * 128 * (bk + 8) * 2); }
+// slice at TE = 128, for slices of bk (with 64-deep slices it also holds
+// the three stages of a wide bf16 tile and the fp32 tile's two buffers; 32-deep
+// slices, one of those buffers), plus the fp32 tile's minima.  The light
+// variant only needs the drain scratch.
+constexpr uint32_t smem_bytes(int bk) { return 2 * (2 * 128 * (bk + 8) * 2) + 32; }
 static_assert(smem_bytes(kBf16SliceK) >= kWideSmemBytes, "wide bf16 tiles fit the full LDS");
+static_assert(smem_bytes(kBf16SliceK) >= 2 * kF32BufBytes + 24 &&
+                  smem_bytes(32) >= kF32BufBytes + 24,
+              "fp32 tiles fit");
 
-// The square matrix tiles as calls, for the wide variant: inlined next to
-// the wide tile their registers would spill.  A call costs a register save
-// and restore per claimed run.
+// The square matrix tiles as calls, for the drain's full variant: inlined next
+// to the 128 x 256 tile their registers would spill.  Called from one kernel
+// only: with a second caller the calls save and restore the registers that
+// the tiles use (fp32 batch 2428 -> 2514 us).
 __device__ __noinline__ void gemm_bf16_tile_call(const uint16_t* A, const uint16_t* B, float* C,
                                                  uint32_t n, uint32_t te, uint32_t tile,
-                                                 uint32_t count, uint16_t* smem) {
+                                                 uint32_t count, lds_u8* smem) {
   if (te == 128) gemm_bf16_tile<128>(A, B, C, n, tile, count, smem);
   else gemm_bf16_tile<64>(A, B, C, n, tile, count, smem);
 }
 __device__ __noinline__ void gemm_f32_tile_call(const float* A, const float* B, float* C,
                                                 uint32_t n, uint32_t te, uint32_t tile,
-                                                uint32_t count, float* smem) {
+                                                uint32_t count, lds_u8* smem) {
   if (te == 128) gemm_f32_tile<128>(A, B, C, n, tile, count, smem);
   else gemm_f32_tile<64>(A, B, C, n, tile, count, smem);
 }
@@ -371,52 +376,39 @@ __device__ __forceinline__ void run_tile(KArgsC& a, const Desc& d, uint32_t tile
 // as one stream (the next tile's first slice loads while the current one
 // finishes), those of a Mandelbrot message as one range of pixel blocks;
 // other behaviours run tile by tile.
+// kWide: the variant with 128 x 256 bf16 tiles.
 template <bool kFull, int kBk = kBf16SliceK, bool kWide = false>
 __device__ __forceinline__ void run_tiles(KArgsC& a, const Desc& d, uint32_t tile,
                                           uint32_t count, uint8_t* smem, uint32_t* lds_ctr) {
-  if constexpr (kWide) {
+  if constexpr (kFull) {
     if (d.behavior == CAF_BHV_GEMM) {
       // work units -> output tiles
       const uint32_t u = gemm_unit(d), all = gemm_tiles(d);
       const uint32_t t0 = tile * u;
       const uint32_t cnt = min(t0 + count * u, all) - t0;
       float* C = reinterpret_cast<float*>(d.out);
-      if (d.flags & DF_BF16) {
-        const uint16_t* A = reinterpret_cast<const uint16_t*>(d.in0);
-        const uint16_t* B = reinterpret_cast<const uint16_t*>(d.in1);
-        if (d.tcfg == 256) gemm_bf16_tile_wide(A, B, C, d.p.g.n, t0, cnt, (uint16_t*)smem);
-        else gemm_bf16_tile_call(A, B, C, d.p.g.n, d.tcfg, t0, cnt, (uint16_t*)smem);
-      } else {
-        gemm_f32_tile_call(reinterpret_cast<const float*>(d.in0),
-                           reinterpret_cast<const float*>(d.in1), C, d.p.g.n, d.tcfg, t0, cnt,
-                           (float*)smem);
-      }
-      return;
-    }
-  } else if constexpr (kFull) {
-    if (d.behavior == CAF_BHV_GEMM) {
-      if (d.tcfg == 256) {  // wide tiles run in the wide variant only
+      const uint16_t* A16 = reinterpret_cast<const uint16_t*>(d.in0);
+      const uint16_t* B16 = reinterpret_cast<const uint16_t*>(d.in1);
+      const float* A = reinterpret_cast<const float*>(d.in0);
+      const float* B = reinterpret_cast<const float*>(d.in1);
+      if constexpr (kWide) {
+        if (!(d.flags & DF_BF16))
+          gemm_f32_tile_call(A, B, C, d.p.g.n, d.tcfg, t0, cnt, (lds_u8*)smem);
+        else if (d.tcfg == 256)
+          gemm_bf16_tile_wide(A16, B16, C, d.p.g.n, t0, cnt, (lds_u8*)smem);
+        else
+          gemm_bf16_tile_call(A16, B16, C, d.p.g.n, d.tcfg, t0, cnt, (lds_u8*)smem);
+      } else if (d.tcfg == 256) {
         if (threadIdx.x == 0) st_dev(&a.sstate[d.slot].status, (int32_t)CAF_E_DEVICE);
-        return;
-      }
-      // work units -> output tiles
-      const uint32_t u = gemm_unit(d), all = gemm_tiles(d);
-      const uint32_t t0 = tile * u;
-      count = min(t0 + count * u, all) - t0;
-      tile = t0;
-      float* C = reinterpret_cast<float*>(d.out);
-      if (d.flags & DF_BF16) {
-        const uint16_t* A = reinterpret_cast<const uint16_t*>(d.in0);
-        const uint16_t* B = reinterpret_cast<const uint16_t*>(d.in1);
+      } else if (d.flags & DF_BF16) {
         if (d.tcfg == 128)
-          gemm_bf16_tile<128, kBk>(A, B, C, d.p.g.n, tile, count, (uint16_t*)smem);
-        else gemm_bf16_tile<64, kBk>(A, B, C, d.p.g.n, tile, count, (uint16_t*)smem);
+          gemm_bf16_tile<128, kBk>(A16, B16, C, d.p.g.n, t0, cnt, (lds_u8*)smem);
+        else
+          gemm_bf16_tile<64, kBk>(A16, B16, C, d.p.g.n, t0, cnt, (lds_u8*)smem);
       } else {
-        const float* A = reinterpret_cast<const float*>(d.in0);
-        const float* B = reinterpret_cast<const float*>(d.in1);
         constexpr int kNBuf = kBk == kBf16SliceK ? 2 : 1;  // the LDS of this variant
-        if (d.tcfg == 128) gemm_f32_tile<128, kNBuf>(A, B, C, d.p.g.n, tile, count, (float*)smem);
-        else gemm_f32_tile<64, kNBuf>(A, B, C, d.p.g.n, tile, count, (float*)smem);
+        if (d.tcfg == 128) gemm_f32_tile<128, kNBuf>(A, B, C, d.p.g.n, t0, cnt, (lds_u8*)smem);
+        else gemm_f32_tile<64, kNBuf>(A, B, C, d.p.g.n, t0, cnt, (lds_u8*)smem);
       }
       return;
     }
@@ -1076,7 +1068,7 @@ enum : uint32_t { CMD_IDLE = 0, CMD_TILE = 1, CMD_DRAIN = 2 };
 constexpr uint32_t kSentinels = 16;
 constexpr uint32_t kHelpRounds = 4;
 
-template <bool kFull, int kBk = kBf16SliceK, bool kWide = false>
+template <bool kFull, int kBk = kBf16SliceK>
 __device__ __forceinline__ void drain_body(KArgsC& a) {
   __shared__ __align__(16) uint8_t smem[kFull ? smem_bytes(kBk) : kSmemLight];
   __shared__ __align__(16) DevSlot s_slot;
@@ -1217,7 +1209,7 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
         // A failed tile stops the message's other tiles; a one-tile message
         // cannot have failed before its tile runs.
         if (ntiles == 1 || s_status == CAF_OK)
-          run_tiles<kFull, kBk, kWide>(a, d, tile, run, smem, &s_ctr);
+          run_tiles<kFull, kBk, kFull && kBk == kBf16SliceK>(a, d, tile, run, smem, &s_ctr);
         wait_stores();
         __syncthreads();
         if (t == 0) s_cont = finish_tiles(a, d, ntiles, run, &s_slot) ? 1u : 0u;
@@ -1309,8 +1301,8 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
 
 // The full variant asks for two waves per SIMD (at most 256 registers,
 // accumulation registers included): two workgroups per compute unit, which
-// suits matrix tiles (64-deep bf16 slices, no register spills in the slice
-// loops).
+// suits matrix tiles (64-deep bf16 slices, the 128 x 256 bf16 tiles' three
+// stages).
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
 drain_kernel_full(KArgs) {
   drain_body<true>(kargs());
@@ -1323,13 +1315,6 @@ drain_kernel_full(KArgs) {
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3)))
 drain_kernel_full3(KArgs) {
   drain_body<true, 32>(kargs());
-}
-
-// The full variant for systems that use 128 x 256 bf16 tiles (two
-// workgroups per compute unit); its square matrix tiles are calls.
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
-drain_kernel_wide(KArgs) {
-  drain_body<true, kBf16SliceK, true>(kargs());
 }
 
 // The light variant asks for five waves per SIMD (at most 96 registers).
@@ -1354,19 +1339,14 @@ const void* plain_kernel_fn(bool full) {
 }
 
 hipError_t launch_drain(const KArgs& a, hipStream_t s) {
-  if (a.full && a.wide)
-    hipLaunchKernelGGL(drain_kernel_wide, dim3(a.grid), dim3(kThreads), 0, s, a);
-  else if (a.full && a.full_wgs == 3)
+  if (a.full && a.full_wgs == 3)
     hipLaunchKernelGGL(drain_kernel_full3, dim3(a.grid), dim3(kThreads), 0, s, a);
   else if (a.full) hipLaunchKernelGGL(drain_kernel_full, dim3(a.grid), dim3(kThreads), 0, s, a);
   else hipLaunchKernelGGL(drain_kernel_light, dim3(a.grid), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 
-hipError_t drain_occupancy(bool full, uint32_t full_wgs, bool wide, int* blocks_per_cu) {
-  if (full && wide)
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, drain_kernel_wide,
-                                                        kThreads, 0);
+hipError_t drain_occupancy(bool full, uint32_t full_wgs, int* blocks_per_cu) {
   if (full && full_wgs == 3)
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, drain_kernel_full3,
                                                         kThreads, 0);

@@ -42,7 +42,7 @@
 namespace cafgpu {
 hipError_t launch_plain(const KArgs& a, const Desc& d, uint32_t ntiles, hipStream_t s);
 hipError_t launch_drain(const KArgs& a, hipStream_t s);
-hipError_t drain_occupancy(bool full, uint32_t full_wgs, bool wide, int* blocks_per_cu);
+hipError_t drain_occupancy(bool full, uint32_t full_wgs, int* blocks_per_cu);
 const void* plain_kernel_fn(bool full);
 }  // namespace cafgpu
 
@@ -291,6 +291,7 @@ struct caf_gpu_system {
   std::atomic<uint64_t> st_completions{0}, st_dup{0}, st_swallowed{0};
   alignas(64) uint32_t mandel_tile_px = 1024;
   uint32_t gemm_tile = 0;
+  bool wide_asked = false;  // a tile choice of 256, ring modes
   uint32_t grid_full = 0, grid_light = 0;  // drain-kernel workgroups per variant
   std::atomic<bool> need_full{false};       // a GEMM actor exists
   std::atomic<bool> held{false};            // caf_gpu_hold: no new drain launch
@@ -653,41 +654,41 @@ int check_signature(const ActorRec& a, const void* args, uint64_t args_bytes, co
   return CAF_E_INVALID;
 }
 
-// Tile choice of a product (tcfg).  A system that runs the wide drain
-// variant gives 256 (128 x 256 bf16 tiles) to every product that qualifies
-// -- bf16 inputs, n % 32 == 0, 16-byte aligned device inputs (host inputs
-// are staged into the arena, which is) -- whatever its size class asks for:
-// in that variant the square tiles are calls.  Other products get their
-// class's edge, 128 where that is 256.
+// Tile choice of a product (tcfg): 256 stands for 128 x 256 bf16 tiles, for
+// n % 32 == 0 and 16-byte aligned device inputs (host inputs are staged into
+// the arena, which is), in the ring modes with two full workgroups per compute
+// unit (their LDS holds the tile's three stages).  A system whose configuration names 256
+// anywhere gives them to every product that qualifies; other products get
+// their class's edge, 128 where that is 256.
 //
-// Without a choice by the caller, the edge follows the load: `ahead` messages
-// are out and not answered.  An fp32 product alone, or with the 128-tiles of
-// all of them filling less than an eighth of the grid (the first of a burst
-// would be cut small otherwise), is cut into 64-tiles (one product alone:
-// n = 256 28 against 36 us, 1024 69 against 116, 1536 132 against 170; at
-// 2048 193 against 208, but two at once 315 against 237); with the chip busy 128 is better from n = 65 on
-// (1,024 products of 128: 168 against 256 us).  bf16 tiles are short: 128
-// always.  The edge does not change the sums.
+// Without a choice by the caller, the tile follows the load: `ahead` messages
+// are out and not answered.  128 x 256 read fewer operand bytes and are used
+// when the products together fill the grid with them (148 products of
+// n = 512 141 us against 176 with 128 x 128, one of 4096 198 against 241; but
+// two of 2048 110 against 81).  An fp32 product alone, or with the 128-tiles
+// of all of them filling less than an eighth of the grid (the first of a
+// burst would be cut small otherwise), is cut into 64-tiles (one product
+// alone: n = 256 28 against 36 us, 1024 69 against 116, 1536 132 against 170;
+// at 2048 193 against 208, but two at once 315 against 237); with the chip
+// busy 128 is better from n = 65 on (1,024 products of 128: 168 against
+// 256 us).  bf16 tiles are short: 128 always.  The tile does not change the
+// sums.
 uint32_t gemm_tile_for(const caf_gpu_system* s, const caf_gemm_args* g, const caf_buf* in,
                        uint64_t ahead) {
   const uint32_t n = g->n;
-  if (s->kargs.wide && g->in_dtype == CAF_BF16 && n % 32 == 0) {
+  const uint32_t cls = n <= 64 ? 0u : n <= 128 ? 1u : n <= 256 ? 2u : 3u;
+  const uint32_t asked = s->gemm_tile ? s->gemm_tile : s->cfg.gemm_tile_class[cls];
+  const uint64_t e = (n + 127) / 128;
+  if (g->in_dtype == CAF_BF16 && n % 32 == 0 && s->kargs.full_wgs == 2 && !s->plain() &&
+      (s->wide_asked || (!asked && n > 64 && (ahead + 1) * e * ((n + 255) / 256) >= s->grid_full))) {
     bool aligned = true;
     for (int i = 0; i < 2; ++i)
       if (in[i].on_device && ((uintptr_t)in[i].data & 15u) != 0) aligned = false;
     if (aligned) return 256;
   }
-  uint32_t t = s->gemm_tile;
-  if (t == 0) {
-    const uint32_t cls = n <= 64 ? 0u : n <= 128 ? 1u : n <= 256 ? 2u : 3u;
-    t = s->cfg.gemm_tile_class[cls];
-    if (t == 0) {
-      const uint64_t e = (n + 127) / 128;
-      const bool idle = (ahead + 1) * e * e < s->grid_full / (ahead ? 8 : 3);
-      t = n <= 64 || (g->in_dtype == CAF_F32 && idle) ? 64u : 128u;
-    }
-  }
-  return t == 256 ? 128u : t;
+  if (asked) return asked == 256 ? 128u : asked;
+  const bool idle = (ahead + 1) * e * e < s->grid_full / (ahead ? 8 : 3);
+  return n <= 64 || (g->in_dtype == CAF_F32 && idle) ? 64u : 128u;
 }
 
 // Output tiles per work unit of a product of `tiles` tiles.  A product that
@@ -1147,15 +1148,8 @@ int caf_gpu_init(const caf_gpu_config* cfg, caf_gpu_system** out) {
   s->mandel_tile_px = mpx;
   s->gemm_tile = cfg->gemm_tile;
   s->kargs.full_wgs = cfg->full_wgs_per_cu == 3 ? 3u : 2u;
-  {
-    // 128 x 256 bf16 tiles: asked for by a tile choice of 256, in a ring
-    // mode with two full workgroups per CU (their LDS holds the tile's
-    // three stages); full launches then use the wide variant.
-    bool asked = cfg->gemm_tile == 256;
-    for (uint32_t t : cfg->gemm_tile_class) asked = asked || t == 256;
-    const bool ring = cfg->mode != CAF_MODE_PLAIN && cfg->mode != CAF_MODE_PLAIN_GRAPH;
-    s->kargs.wide = asked && ring && s->kargs.full_wgs == 2 ? 1u : 0u;
-  }
+  s->wide_asked = cfg->gemm_tile == 256;
+  for (uint32_t t : cfg->gemm_tile_class) s->wide_asked = s->wide_asked || t == 256;
   s->arena.init((uint64_t)(uintptr_t)cfg->arena, cfg->arena_bytes);
   bool ok = true;
   auto chk = [&](hipError_t e) {
@@ -1210,8 +1204,8 @@ int caf_gpu_init(const caf_gpu_config* cfg, caf_gpu_system** out) {
   // Default grid: every workgroup resident (the kernel never needs that,
   // but it is the most work in flight).
   int occ_full = 1, occ_light = 1;
-  if (ok) chk(drain_occupancy(true, s->kargs.full_wgs, s->kargs.wide != 0, &occ_full));
-  if (ok) chk(drain_occupancy(false, s->kargs.full_wgs, false, &occ_light));
+  if (ok) chk(drain_occupancy(true, s->kargs.full_wgs, &occ_full));
+  if (ok) chk(drain_occupancy(false, s->kargs.full_wgs, &occ_light));
   if (occ_full < 1) occ_full = 1;
   if (occ_light < 1) occ_light = 1;
   s->grid_full = cfg->grid ? cfg->grid : (uint32_t)(cus * occ_full);

@@ -30,7 +30,13 @@ template <typename T>
 __device__ __forceinline__ CAF_GLOBAL T* global_ptr(T* p) {
   return (CAF_GLOBAL T*)p;
 }
+// LDS (address space 3) views, for the same reason: the matrix tiles are
+// called from several kernels, and through a generic pointer their LDS
+// accesses would be flat_* instructions too.
+#define CAF_LDS __attribute__((address_space(3)))
+typedef CAF_LDS uint8_t lds_u8;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // A 16-byte global load, returned as V (float4 or uint4).
 template <typename V, typename T>
 __device__ __forceinline__ V load_global(const CAF_GLOBAL T* p) {
@@ -362,6 +368,8 @@ __device__ __noinline__ void gemm_f32_direct(const float* A, const float* B, flo
 constexpr uint32_t kSplitMinExp = 127 - 103;
 constexpr uint32_t kSplitMinExpSum = 2 * 127 - 100;
 
+constexpr uint32_t kF32BufBytes = 36864;
+
 // The part of a tile stream that one wave runs: the waves that load A and
 // those that load B differ in how they split and store a slice, and each has
 // its own copy of the loop, so that a step is one basic block in which the
@@ -371,8 +379,8 @@ template <int TE, int NBUF, bool kA>
 __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
                                                 const float* __restrict__ B,
                                                 float* __restrict__ C, uint32_t n, uint32_t tile0,
-                                                uint32_t count, uint8_t* lds,
-                                                uint32_t (*s_min)[2]) {
+                                                uint32_t count, lds_u8* lds,
+                                                CAF_LDS uint32_t (*s_min)[2]) {
   constexpr uint32_t WB = TE / 64;           // 32 x 32 blocks per wave and dimension
   constexpr uint32_t SUB = 128 / TE;         // 16 deep sub-slices per slice
   constexpr uint32_t KS = 16 * SUB;          // k per slice
@@ -380,7 +388,7 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
   constexpr uint32_t PLANE = TE * ROW;       // one term of one operand, one sub-slice
   constexpr uint32_t OPND = 3 * PLANE;       // its three terms
   constexpr uint32_t BUF = SUB * 2 * OPND;   // bytes of an LDS buffer
-  static_assert(BUF == 36864, "slice buffer");
+  static_assert(BUF == kF32BufBytes, "slice buffer");
   const auto Cg = global_ptr(C);
   const auto src = reinterpret_cast<const CAF_GLOBAL uint8_t*>(global_ptr(kA ? A : B));
   const uint32_t t = threadIdx.x, lane = lane_id(), w = wave_id();
@@ -488,8 +496,8 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
   };
   const uint32_t dst0 = kA ? (a_k >> 4) * (2 * OPND) + a_row * ROW + (a_k & 15u) * 2
                            : (b_k >> 4) * (2 * OPND) + OPND + b_col * ROW + (b_k & 15u) * 2;
-  auto lstore = [&](const Slice& s, uint8_t* buf) {
-    uint8_t* dst = buf + dst0;
+  auto lstore = [&](const Slice& s, lds_u8* buf) {
+    lds_u8* dst = buf + dst0;
 #pragma unroll
     for (uint32_t q = 0; q < 4; ++q) {  // row q of A, column q of B
       uint32_t lo[3], hi[3];
@@ -497,31 +505,33 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
       split(kA ? s.v[q][2] : s.v[2][q], kA ? s.v[q][3] : s.v[3][q], hi);
 #pragma unroll
       for (uint32_t p = 0; p < 3; ++p)
-        *reinterpret_cast<uint2*>(dst + p * PLANE + q * (kA ? TE / 4 : 1) * ROW) =
-            make_uint2(lo[p], hi[p]);
+        *reinterpret_cast<CAF_LDS u32x2*>(dst + p * PLANE + q * (kA ? TE / 4 : 1) * ROW) =
+            u32x2{lo[p], hi[p]};
     }
   };
   auto note_min = [&](uint32_t tseq) {  // the tile's last slice is in LDS
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) vmin = min(vmin, (uint32_t)__shfl_xor((int)vmin, off));
-    if (lane == 0) atomicMin(&s_min[tseq % 3][kA ? 0 : 1], vmin);
+    if (lane == 0)
+      __hip_atomic_fetch_min(&s_min[tseq % 3][kA ? 0 : 1], vmin, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WORKGROUP);
     vmin = 0xFFFFFFFFu;
   };
-  auto mfma_slice = [&](const uint8_t* buf) {
+  auto mfma_slice = [&](const lds_u8* buf) {
 #pragma unroll
     for (uint32_t sub = 0; sub < SUB; ++sub) {
-      const uint8_t* As = buf + sub * (2 * OPND) + (lane >> 5) * 16;
-      const uint8_t* Bs = As + OPND;
+      const lds_u8* As = buf + sub * (2 * OPND) + (lane >> 5) * 16;
+      const lds_u8* Bs = As + OPND;
       bf16x8 a[3][WB], b[3][WB];
 #pragma unroll
       for (uint32_t p = 0; p < 3; ++p)
 #pragma unroll
         for (uint32_t i = 0; i < WB; ++i) {
           a[p][i] = __builtin_bit_cast(
-              bf16x8, *reinterpret_cast<const uint4*>(
+              bf16x8, *reinterpret_cast<const CAF_LDS u32x4*>(
                           As + p * PLANE + (wm * (TE / 2) + i * 32 + (lane & 31)) * ROW));
           b[p][i] = __builtin_bit_cast(
-              bf16x8, *reinterpret_cast<const uint4*>(
+              bf16x8, *reinterpret_cast<const CAF_LDS u32x4*>(
                           Bs + p * PLANE + (wn * (TE / 2) + i * 32 + (lane & 31)) * ROW));
         }
       // the small terms first
@@ -632,17 +642,17 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
 
 // NBUF: LDS buffers (2, or 1 where the kernel variant has half the LDS).
 // One call computes `count` consecutive output tiles (row-major tile order)
-// of one product, as one stream of slices.  smem: NBUF x 36 KB.
+// of one product, as one stream of slices.  smem: NBUF x 36 KB and 24 bytes.
 template <int TE, int NBUF = 2>
 __device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A,
                                               const float* __restrict__ B,
                                               float* __restrict__ C, uint32_t n, uint32_t tile0,
-                                              uint32_t count, float* smem) {
+                                              uint32_t count, lds_u8* smem) {
   // smallest non-zero magnitude of the tile's A and B, as (bits << 1) - 1;
   // three tiles in turn, so that one is cleared while the next is in use
-  __shared__ uint32_t s_min[3][2];
+  CAF_LDS uint32_t(*s_min)[2] =
+      reinterpret_cast<CAF_LDS uint32_t(*)[2]>(smem + NBUF * kF32BufBytes);
   const uint32_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(wave_id());
-  uint8_t* lds = reinterpret_cast<uint8_t*>(smem);
   if (n < 4) {  // one tile
     if (w == 0) gemm_f32_direct(A, B, C, n, 0, 0);
     __syncthreads();
@@ -650,8 +660,8 @@ __device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A,
   }
   if (t < 6) s_min[t >> 1][t & 1u] = 0xFFFFFFFFu;
   __syncthreads();
-  if (w < 2) gemm_f32_stream<TE, NBUF, true>(A, B, C, n, tile0, count, lds, s_min);
-  else gemm_f32_stream<TE, NBUF, false>(A, B, C, n, tile0, count, lds, s_min);
+  if (w < 2) gemm_f32_stream<TE, NBUF, true>(A, B, C, n, tile0, count, smem, s_min);
+  else gemm_f32_stream<TE, NBUF, false>(A, B, C, n, tile0, count, smem, s_min);
 }
 
 // bfloat16 inputs: v_mfma_f32_32x32x16_bf16, k slices of kBf16SliceK.  Both operands
@@ -670,7 +680,9 @@ constexpr int kBf16SliceK = 64;
 template <int TE, int BK = kBf16SliceK>
 __device__ __forceinline__ void gemm_bf16_tile(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                float* __restrict__ C, uint32_t n, uint32_t tile0,
-                               uint32_t count, uint16_t* smem) {
+                               uint32_t count, lds_u8* smem8) {
+  typedef CAF_LDS uint16_t lds_u16;
+  lds_u16* smem = reinterpret_cast<lds_u16*>(smem8);
   constexpr int LD = BK + 8;
   constexpr int WB = TE / 64;
   constexpr int QA = TE * BK / 8 / kThreads;  // 16-byte A chunks per thread
@@ -699,7 +711,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const uint16_t* __restrict__ A, c
         store_c<TE>(Cg, n, tm * TE + wm * (TE / 2) + i * 32, tn * TE + wn * (TE / 2) + j * 32,
                     acc[i][j]);
   };
-  auto mfma_slice = [&](const uint16_t* As, const uint16_t* Bs) {
+  auto mfma_slice = [&](const lds_u16* As, const lds_u16* Bs) {
 #pragma unroll
     for (int ks = 0; ks < BK; ks += 16) {
       const uint32_t kc = ks + 8 * (lane >> 5);
@@ -707,12 +719,12 @@ __device__ __forceinline__ void gemm_bf16_tile(const uint16_t* __restrict__ A, c
 #pragma unroll
       for (int i = 0; i < WB; ++i)
         a[i] = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const uint4*>(
+            bf16x8, *reinterpret_cast<const CAF_LDS u32x4*>(
                         As + (wm * (TE / 2) + i * 32 + (lane & 31)) * LD + kc));
 #pragma unroll
       for (int j = 0; j < WB; ++j)
         b[j] = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const uint4*>(
+            bf16x8, *reinterpret_cast<const CAF_LDS u32x4*>(
                         Bs + (wn * (TE / 2) + j * 32 + (lane & 31)) * LD + kc));
 #pragma unroll
       for (int i = 0; i < WB; ++i)
@@ -773,7 +785,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const uint16_t* __restrict__ A, c
         rb[r] = load_global<uint4>(pb + (uint64_t)row * n);
       }
     };
-    auto lstore = [&](uint16_t* buf, uint32_t k0, bool checked) {
+    auto lstore = [&](lds_u16* buf, uint32_t k0, bool checked) {
       if (checked) {
         const uint4 z = make_uint4(0, 0, 0, 0);
 #pragma unroll
@@ -783,12 +795,13 @@ __device__ __forceinline__ void gemm_bf16_tile(const uint16_t* __restrict__ A, c
         for (int r = 0; r < 4; ++r)
           if (k0 + kb * 4 + r >= n) rb[r] = z;
       }
-      uint16_t* As = buf;
-      uint16_t* Bs = buf + TE * LD;
+      lds_u16* As = buf;
+      lds_u16* Bs = buf + TE * LD;
 #pragma unroll
       for (int q = 0; q < QA; ++q) {
         const uint32_t idx = t + kThreads * q;
-        *reinterpret_cast<uint4*>(As + (idx / (BK / 8)) * LD + kca[q]) = ra[q];
+        *reinterpret_cast<CAF_LDS u32x4*>(As + (idx / (BK / 8)) * LD + kca[q]) =
+            __builtin_bit_cast(u32x4, ra[q]);
       }
       if (has_b) {
         // column c of the block: k pairs (2m, 2m+1) from rows 2m and 2m+1,
@@ -803,7 +816,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const uint16_t* __restrict__ A, c
             const uint32_t wh = (c >> 1) == 0 ? hi.x : (c >> 1) == 1 ? hi.y : (c >> 1) == 2 ? hi.z : hi.w;
             col[m] = __builtin_amdgcn_perm(wh, wl, (c & 1) ? 0x07060302u : 0x05040100u);
           }
-          *reinterpret_cast<uint2*>(Bs + (nb * 8 + c) * LD + kb * 4) = make_uint2(col[0], col[1]);
+          *reinterpret_cast<CAF_LDS u32x2*>(Bs + (nb * 8 + c) * LD + kb * 4) = u32x2{col[0], col[1]};
         }
       }
     };
@@ -834,7 +847,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const uint16_t* __restrict__ A, c
       // keep the prefetch ahead of the matrix instructions (the scheduler
       // would otherwise sink the loads to shorten their registers' lives)
       __builtin_amdgcn_sched_barrier(0);
-      const uint16_t* buf = smem + cur * SLICE;
+      const lds_u16* buf = smem + cur * SLICE;
       mfma_slice(buf, buf + TE * LD);
       if (tile_ends) {
         store_tile(otm, otn);
@@ -847,14 +860,14 @@ __device__ __forceinline__ void gemm_bf16_tile(const uint16_t* __restrict__ A, c
       k = k1;
     }
     {
-      const uint16_t* buf = smem + cur * SLICE;
+      const lds_u16* buf = smem + cur * SLICE;
       mfma_slice(buf, buf + TE * LD);
       store_tile(tm, tn);
     }
   } else {
     // ragged or unaligned operands: element loads, one buffer, tile by tile
-    uint16_t* As = smem;
-    uint16_t* Bs = smem + TE * LD;
+    lds_u16* As = smem;
+    lds_u16* Bs = smem + TE * LD;
     for (uint32_t i = 0; i < count; ++i) {
       uint32_t tm, tn;
       tile_coords(tile0 + i, n, TE, tm, tn);
@@ -927,18 +940,15 @@ __device__ __forceinline__ void barrier_no_fence() {
 __device__ __forceinline__ void gemm_bf16_tile_wide(const uint16_t* __restrict__ A,
                                                     const uint16_t* __restrict__ B,
                                                     float* __restrict__ C, uint32_t n,
-                                                    uint32_t tile0, uint32_t count, uint16_t* smem) {
+                                                    uint32_t tile0, uint32_t count, lds_u8* lds) {
   constexpr uint32_t TM = 128, TN = 256, BK = 32, WM = 2, WN = 4, NS = kWideStages;
   constexpr uint32_t A_BYTES = TM * BK * 2, B_BYTES = BK * TN * 2, STAGE = A_BYTES + B_BYTES;
   constexpr uint32_t LOADS = (A_BYTES + B_BYTES) / 16 / kThreads;  // direct loads per thread and slice
-  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-  typedef __attribute__((address_space(3))) uint8_t lds_u8;
   const auto Ag = global_ptr(A);
   const auto Bg = global_ptr(B);
   const auto Cg = global_ptr(C);
   const uint32_t t = threadIdx.x, lane = lane_id(), w = wave_id();
   const uint32_t wm = w >> 1, wn = w & 1;
-  lds_u8* lds = (lds_u8*)smem;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
   floatx16 acc[WM][WN];
   auto zero_acc = [&]() {
