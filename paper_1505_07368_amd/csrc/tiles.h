@@ -37,6 +37,7 @@ __device__ __forceinline__ CAF_GLOBAL T* global_ptr(T* p) {
 typedef CAF_LDS uint8_t lds_u8;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4a2 __attribute__((ext_vector_type(4), aligned(2)));
 // A 16-byte global load, returned as V (float4 or uint4).
 template <typename V, typename T>
 __device__ __forceinline__ V load_global(const CAF_GLOBAL T* p) {
@@ -687,13 +688,22 @@ __device__ __forceinline__ void gemm_bf16_tile(const uint16_t* __restrict__ A, c
   constexpr int WB = TE / 64;
   constexpr int QA = TE * BK / 8 / kThreads;  // 16-byte A chunks per thread
   constexpr int SLICE = 2 * TE * LD;          // bf16 per LDS buffer
-  const auto Ag = global_ptr(A);
-  const auto Bg = global_ptr(B);
+  const auto Ag = reinterpret_cast<const CAF_GLOBAL uint8_t*>(global_ptr(A));
+  const auto Bg = reinterpret_cast<const CAF_GLOBAL uint8_t*>(global_ptr(B));
   const auto Cg = global_ptr(C);
   const uint32_t t = threadIdx.x, lane = lane_id(), w = wave_id();
   const uint32_t wm = w >> 1, wn = w & 1;
-  const bool vec = (n % 8u) == 0 && ((reinterpret_cast<uintptr_t>(A) |
-                                      reinterpret_cast<uintptr_t>(B)) & 15u) == 0;
+  if (n < 3) {  // fewer than eight elements: no 16-byte loads
+    if (t < n * n) {
+      auto f = [](uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); };
+      const uint32_t r = t / n, c = t % n;
+      float x = f(A[r * n]) * f(B[c]);  // exact
+      if (n == 2) x = __builtin_fmaf(f(A[r * n + 1]), f(B[n + c]), x);
+      store_reply(Cg + t, x);
+    }
+    __syncthreads();
+    return;
+  }
   floatx16 acc[WB][WB];
   auto zero_acc = [&]() {
 #pragma unroll
@@ -735,158 +745,142 @@ __device__ __forceinline__ void gemm_bf16_tile(const uint16_t* __restrict__ A, c
   };
   zero_acc();
 
-  if (vec) {
-    // The tiles of the range run as one stream of 64-deep slices: while the
-    // matrix cores work on one slice, the next one (possibly the first of
-    // the next tile) is already being loaded, so a tile's first loads and
-    // its output stores overlap its neighbours' work.
-    //
-    // Every load is issued unconditionally from an address inside the
-    // matrix, so the registers it fills have a single definition and the
-    // compiler need not wait for the prefetch before the current slice's
-    // matrix instructions.  Rows of A and columns of B outside the matrix
-    // are clamped to valid ones: they only feed rows / columns of C that are
-    // not stored.  k runs past n only in a partial last slice; there the
-    // loads read clamped addresses and lstore() writes zeros instead.  With
-    // TE = 64 only half the threads own a B block; the others load a valid
-    // block and skip its store.
-    constexpr int NB4 = (BK / 4) * (TE / 8);  // 4 (k) x 8 (n) blocks of B per slice
-    static_assert(NB4 <= kThreads, "one B block per thread at most");
-    const uint32_t kb = t % (BK / 4), nb = (t / (BK / 4)) % (TE / 8);  // k-block fastest
-    const bool has_b = NB4 == kThreads || t < (uint32_t)NB4;
-    uint32_t kca[QA];
+  // The tiles of the range run as one stream of 64-deep slices: while the
+  // matrix cores work on one slice, the next one (possibly the first of
+  // the next tile) is already being loaded, so a tile's first loads and
+  // its output stores overlap its neighbours' work.
+  //
+  // Every load is 16 bytes, at any alignment of elements (products of
+  // n % 8 != 0 were loaded element by element: 1,024 of n = 500 6.4 ms, now
+  // as n = 512's), and issued unconditionally from an address inside the
+  // matrix, so the registers it fills have a single definition and the
+  // compiler need not wait for the prefetch before the current slice's
+  // matrix instructions.  A load past the end of a row reads the next row's
+  // first elements, one past the matrix its last eight.  Rows of A and
+  // columns of B outside the matrix only feed rows / columns of C that are
+  // not stored; k beyond n is put right in lstore(), in a tile's last slice.
+  // With TE = 64 only half the threads own a B block; the others load a
+  // block and skip its store.
+  constexpr int NB4 = (BK / 4) * (TE / 8);  // 4 (k) x 8 (n) blocks of B per slice
+  static_assert(NB4 <= kThreads, "one B block per thread at most");
+  const uint32_t kb = t % (BK / 4), nb = (t / (BK / 4)) % (TE / 8);  // k-block fastest
+  const bool has_b = NB4 == kThreads || t < (uint32_t)NB4;
+  uint32_t kca[QA];
 #pragma unroll
-    for (int q = 0; q < QA; ++q) kca[q] = ((t + kThreads * q) % (BK / 8)) * 8;
-    const CAF_GLOBAL uint16_t* pa[QA];  // row starts of this thread's A chunks
-    const CAF_GLOBAL uint16_t* pb;      // column of this thread's B block
-    auto sources = [&](uint32_t tm, uint32_t tn) {
+  for (int q = 0; q < QA; ++q) kca[q] = ((t + kThreads * q) % (BK / 8)) * 8;
+  const uint32_t last8 = n * n - 8u;
+  uint32_t ao[QA], bo;  // element offsets of this thread's loads at k = 0
+  auto sources = [&](uint32_t tm, uint32_t tn) {
 #pragma unroll
-      for (int q = 0; q < QA; ++q) {
-        const uint32_t row = (t + kThreads * q) / (BK / 8);
-        pa[q] = Ag + (uint64_t)min(tm * TE + row, n - 1u) * n;
-      }
-      uint32_t gcol = tn * TE + nb * 8;
-      if (gcol >= n) gcol = 0;
-      pb = Bg + gcol;
-    };
-    uint4 ra[QA], rb[4];
-    // checked: the slice at k0 may run past n (uniform)
-    auto gload = [&](uint32_t k0, bool checked) {
+    for (int q = 0; q < QA; ++q)
+      ao[q] = (tm * TE + (t + kThreads * q) / (BK / 8)) * n + kca[q];
+    bo = kb * 4 * n + tn * TE + nb * 8;
+  };
+  auto load8 = [&](const CAF_GLOBAL uint8_t* base, uint32_t o) {
+    return __builtin_bit_cast(
+        uint4, (u32x4)*reinterpret_cast<const CAF_GLOBAL u32x4a2*>(base + min(o, last8) * 2u));
+  };
+  uint4 ra[QA], rb[4];
+  auto gload = [&](uint32_t k0) {
 #pragma unroll
-      for (int q = 0; q < QA; ++q) {
-        // a chunk past the last k reads the row's first chunk instead
-        const uint32_t col = (!checked || k0 + kca[q] < n) ? k0 + kca[q] : 0u;
-        ra[q] = load_global<uint4>(pa[q] + col);
-      }
+    for (int q = 0; q < QA; ++q) ra[q] = load8(Ag, ao[q] + k0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        uint32_t row = k0 + kb * 4 + r;
-        row = checked ? min(row, n - 1u) : row;
-        rb[r] = load_global<uint4>(pb + (uint64_t)row * n);
-      }
-    };
-    auto lstore = [&](lds_u16* buf, uint32_t k0, bool checked) {
-      if (checked) {
-        const uint4 z = make_uint4(0, 0, 0, 0);
+    for (int r = 0; r < 4; ++r) rb[r] = load8(Bg, bo + (k0 + r) * n);
+  };
+  // elements d .. 7 moved to the front (the load was clamped by d)
+  auto moved = [](uint4 v, uint32_t d) {
+    const unsigned __int128 x = __builtin_bit_cast(unsigned __int128, v);
+    return __builtin_bit_cast(uint4, d < 8 ? x >> (16 * d) : (unsigned __int128)0);
+  };
+  // the first m elements kept
+  auto first = [](uint4 v, uint32_t m) {
+    const unsigned __int128 x = __builtin_bit_cast(unsigned __int128, v);
+    return __builtin_bit_cast(uint4, m < 8 ? x & (((unsigned __int128)1 << (16 * m)) - 1) : x);
+  };
+  // the slice's place in its tile's sources (ao, bo) is still that of the
+  // slice stored: a tile's last slice is stored before its successor loads
+  auto fix = [&](uint32_t k0) {
 #pragma unroll
-        for (int q = 0; q < QA; ++q)
-          if (k0 + kca[q] >= n) ra[q] = z;
+    for (int q = 0; q < QA; ++q) {
+      const uint32_t o = ao[q] + k0, k = k0 + kca[q];
+      ra[q] = first(moved(ra[q], o - min(o, last8)), k < n ? n - k : 0u);
+    }
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (k0 + kb * 4 + r >= n) rb[r] = z;
-      }
-      lds_u16* As = buf;
-      lds_u16* Bs = buf + TE * LD;
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t o = bo + (k0 + r) * n;
+      rb[r] = k0 + kb * 4 + r < n ? moved(rb[r], o - min(o, last8)) : make_uint4(0, 0, 0, 0);
+    }
+  };
+  auto lstore = [&](lds_u16* buf, uint32_t k0, bool checked) {
+    if (checked) fix(k0);
+    lds_u16* As = buf;
+    lds_u16* Bs = buf + TE * LD;
 #pragma unroll
-      for (int q = 0; q < QA; ++q) {
-        const uint32_t idx = t + kThreads * q;
-        *reinterpret_cast<CAF_LDS u32x4*>(As + (idx / (BK / 8)) * LD + kca[q]) =
-            __builtin_bit_cast(u32x4, ra[q]);
-      }
-      if (has_b) {
-        // column c of the block: k pairs (2m, 2m+1) from rows 2m and 2m+1,
-        // low halves for even c, high halves for odd c
+    for (int q = 0; q < QA; ++q) {
+      const uint32_t idx = t + kThreads * q;
+      *reinterpret_cast<CAF_LDS u32x4*>(As + (idx / (BK / 8)) * LD + kca[q]) =
+          __builtin_bit_cast(u32x4, ra[q]);
+    }
+    if (has_b) {
+      // column c of the block: k pairs (2m, 2m+1) from rows 2m and 2m+1,
+      // low halves for even c, high halves for odd c
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          uint32_t col[2];
+      for (int c = 0; c < 8; ++c) {
+        uint32_t col[2];
 #pragma unroll
-          for (int m = 0; m < 2; ++m) {
-            const uint4 lo = rb[2 * m], hi = rb[2 * m + 1];
-            const uint32_t wl = (c >> 1) == 0 ? lo.x : (c >> 1) == 1 ? lo.y : (c >> 1) == 2 ? lo.z : lo.w;
-            const uint32_t wh = (c >> 1) == 0 ? hi.x : (c >> 1) == 1 ? hi.y : (c >> 1) == 2 ? hi.z : hi.w;
-            col[m] = __builtin_amdgcn_perm(wh, wl, (c & 1) ? 0x07060302u : 0x05040100u);
-          }
-          *reinterpret_cast<CAF_LDS u32x2*>(Bs + (nb * 8 + c) * LD + kb * 4) = u32x2{col[0], col[1]};
+        for (int m = 0; m < 2; ++m) {
+          const uint4 lo = rb[2 * m], hi = rb[2 * m + 1];
+          const uint32_t wl = (c >> 1) == 0 ? lo.x : (c >> 1) == 1 ? lo.y : (c >> 1) == 2 ? lo.z : lo.w;
+          const uint32_t wh = (c >> 1) == 0 ? hi.x : (c >> 1) == 1 ? hi.y : (c >> 1) == 2 ? hi.z : hi.w;
+          col[m] = __builtin_amdgcn_perm(wh, wl, (c & 1) ? 0x07060302u : 0x05040100u);
         }
+        *reinterpret_cast<CAF_LDS u32x2*>(Bs + (nb * 8 + c) * LD + kb * 4) = u32x2{col[0], col[1]};
       }
-    };
-    const uint32_t nk = (n + BK - 1) / BK;   // slices per tile
-    const uint32_t last = nk - 1;            // the only slice that can be partial
-    const bool ragged = (n % BK) != 0;
-    const uint32_t steps = count * nk;
-    uint32_t tile = tile0, k = 0, tm, tn;
-    tile_coords(tile, n, TE, tm, tn);
-    sources(tm, tn);
-    gload(0, ragged && last == 0);
-    lstore(smem, 0, ragged && last == 0);
+    }
+  };
+  const uint32_t nk = (n + BK - 1) / BK;   // slices per tile
+  const uint32_t last = nk - 1;            // the only slice that can be partial
+  const bool ragged = (n % BK) != 0;
+  const uint32_t steps = count * nk;
+  uint32_t tile = tile0, k = 0, tm, tn;
+  tile_coords(tile, n, TE, tm, tn);
+  sources(tm, tn);
+  gload(0);
+  lstore(smem, 0, ragged && last == 0);
+  __syncthreads();
+  uint32_t cur = 0;
+  // Step s computes slice k of `tile` from LDS buffer `cur` and prefetches
+  // step s + 1.  The last step is peeled off so that every iteration
+  // issues its prefetch unconditionally.
+  for (uint32_t s = 0; s + 1 < steps; ++s) {
+    const bool tile_ends = k == last;
+    const uint32_t otm = tm, otn = tn;
+    const uint32_t k1 = tile_ends ? 0u : k + 1;
+    if (tile_ends) {
+      tile_coords(tile + 1, n, TE, tm, tn);
+      sources(tm, tn);
+    }
+    const bool chk = ragged && k1 == last;
+    gload(k1 * BK);
+    // keep the prefetch ahead of the matrix instructions (the scheduler
+    // would otherwise sink the loads to shorten their registers' lives)
+    __builtin_amdgcn_sched_barrier(0);
+    const lds_u16* buf = smem + cur * SLICE;
+    mfma_slice(buf, buf + TE * LD);
+    if (tile_ends) {
+      store_tile(otm, otn);
+      zero_acc();
+      ++tile;
+    }
+    lstore(smem + (cur ^ 1u) * SLICE, k1 * BK, chk);
     __syncthreads();
-    uint32_t cur = 0;
-    // Step s computes slice k of `tile` from LDS buffer `cur` and prefetches
-    // step s + 1.  The last step is peeled off so that every iteration
-    // issues its prefetch unconditionally.
-    for (uint32_t s = 0; s + 1 < steps; ++s) {
-      const bool tile_ends = k == last;
-      const uint32_t otm = tm, otn = tn;
-      const uint32_t k1 = tile_ends ? 0u : k + 1;
-      if (tile_ends) {
-        tile_coords(tile + 1, n, TE, tm, tn);
-        sources(tm, tn);
-      }
-      const bool chk = ragged && k1 == last;
-      gload(k1 * BK, chk);
-      // keep the prefetch ahead of the matrix instructions (the scheduler
-      // would otherwise sink the loads to shorten their registers' lives)
-      __builtin_amdgcn_sched_barrier(0);
-      const lds_u16* buf = smem + cur * SLICE;
-      mfma_slice(buf, buf + TE * LD);
-      if (tile_ends) {
-        store_tile(otm, otn);
-        zero_acc();
-        ++tile;
-      }
-      lstore(smem + (cur ^ 1u) * SLICE, k1 * BK, chk);
-      __syncthreads();
-      cur ^= 1u;
-      k = k1;
-    }
-    {
-      const lds_u16* buf = smem + cur * SLICE;
-      mfma_slice(buf, buf + TE * LD);
-      store_tile(tm, tn);
-    }
-  } else {
-    // ragged or unaligned operands: element loads, one buffer, tile by tile
-    lds_u16* As = smem;
-    lds_u16* Bs = smem + TE * LD;
-    for (uint32_t i = 0; i < count; ++i) {
-      uint32_t tm, tn;
-      tile_coords(tile0 + i, n, TE, tm, tn);
-      if (i) zero_acc();
-      for (uint32_t k0 = 0; k0 < n; k0 += BK) {
-        for (uint32_t idx = t; idx < (uint32_t)(TE * BK); idx += kThreads) {
-          const uint32_t row = idx / BK, kk = idx % BK;
-          const uint32_t gr = tm * TE + row, gk = k0 + kk;
-          As[row * LD + kk] = (gr < n && gk < n) ? Ag[(uint64_t)gr * n + gk] : (uint16_t)0;
-          const uint32_t kr = idx / TE, c = idx % TE;
-          const uint32_t gk2 = k0 + kr, gc = tn * TE + c;
-          Bs[c * LD + kr] = (gk2 < n && gc < n) ? Bg[(uint64_t)gk2 * n + gc] : (uint16_t)0;
-        }
-        __syncthreads();
-        mfma_slice(As, Bs);
-        __syncthreads();
-      }
-      store_tile(tm, tn);
-    }
+    cur ^= 1u;
+    k = k1;
+  }
+  {
+    const lds_u16* buf = smem + cur * SLICE;
+    mfma_slice(buf, buf + TE * LD);
+    store_tile(tm, tn);
   }
 }
 
