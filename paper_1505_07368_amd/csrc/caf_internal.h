@@ -54,7 +54,7 @@ struct alignas(16) Desc {
   uint64_t out;        // 40: ... and of the reply (the kernel's last parameter)
   uint32_t hop_actor[kMaxHops];  // 48: forwarding chain, actor index + 1 (0 = none)
   uint64_t hop_out[kMaxHops];    // 56: reply buffers of the hops
-  uint32_t tcfg;       // 72: work-tile size (GEMM tile edge / Mandelbrot px per tile)
+  uint32_t tcfg;       // 72: work-tile size (GEMM tile edge / Mandelbrot px per tile / ...)
   uint32_t numel;      // 76: echo element count
   union {              // 80: parameter block, 48 bytes
     struct {
@@ -217,6 +217,15 @@ __host__ __device__ inline uint32_t gemm_tiles(const Desc& d) {
   return t * t;
 }
 __host__ __device__ inline uint32_t gemm_unit(const Desc& d) { return d.p.g.unit ? d.p.g.unit : 1u; }
+// Work tiles of the elementwise and the row actor: tcfg x 4096 elements, tcfg
+// rows (0, in forwarded stages: 4096 elements, 16 rows).
+__host__ __device__ inline uint32_t tanh_tile_elems(const Desc& d) {
+  return kTanhTile * (d.tcfg ? d.tcfg : 1u);
+}
+__host__ __device__ inline uint32_t rowsum_tile_rows(const Desc& d) {
+  return d.tcfg ? d.tcfg : kRowsumTile;
+}
+
 // Claimable work units of a message (the drain's "tiles").
 __host__ __device__ inline uint32_t desc_ntiles(const Desc& d) {
   switch (d.behavior) {
@@ -231,11 +240,13 @@ __host__ __device__ inline uint32_t desc_ntiles(const Desc& d) {
       return (gemm_tiles(d) + u - 1) / u;
     }
     case CAF_BHV_TANH: {
-      uint64_t ne = (uint64_t)d.p.s.rows * d.p.s.cols;
-      return (uint32_t)((ne + kTanhTile - 1) / kTanhTile);
+      const uint64_t ne = (uint64_t)d.p.s.rows * d.p.s.cols, te = tanh_tile_elems(d);
+      return (uint32_t)((ne + te - 1) / te);
     }
-    case CAF_BHV_ROWSUM:
-      return (d.p.s.rows + kRowsumTile - 1) / kRowsumTile;
+    case CAF_BHV_ROWSUM: {
+      const uint32_t tr = rowsum_tile_rows(d);
+      return (uint32_t)(((uint64_t)d.p.s.rows + tr - 1) / tr);
+    }
     default:
       return 1;
   }

@@ -348,14 +348,8 @@ __device__ __forceinline__ void run_tile(KArgsC& a, const Desc& d, uint32_t tile
       // the tiles inlined), and a light launch does not drain GEMM messages
       if (threadIdx.x == 0) st_dev(&a.sstate[d.slot].status, (int32_t)CAF_E_DEVICE);
       break;
-    case CAF_BHV_TANH:
-      tanh_tile(reinterpret_cast<const float*>(d.in0), reinterpret_cast<float*>(d.out),
-                (uint64_t)d.p.s.rows * d.p.s.cols, tile);
-      break;
-    case CAF_BHV_ROWSUM:
-      rowsum_tile(reinterpret_cast<const float*>(d.in0), reinterpret_cast<float*>(d.out),
-                  d.p.s.rows, d.p.s.cols, tile);
-      break;
+    case CAF_BHV_TANH: tanh_tile(d, tile, 1u); break;
+    case CAF_BHV_ROWSUM: rowsum_tile<kFull>(d, tile, 1u); break;
     case CAF_BHV_NOOP:
       echo_tile(d, a.slots[d.slot].inline_out);
       break;
@@ -425,9 +419,10 @@ __device__ __forceinline__ void run_tiles(KArgsC& a, const Desc& d, uint32_t til
 }
 
 // A pipeline stage (row-wise tanh or row sum of a float matrix) run inline
-// by the workgroup that finished the previous stage: every tile in turn.
+// by the workgroup that finished the previous stage (whose status was OK).
 // `s_slot` holds the stage's descriptor, `s_flag` is workgroup-shared
 // scratch.  Whole workgroup.
+template <bool kFull>
 __device__ __forceinline__ void run_inline_stages(KArgsC& a, DevSlot& s_slot, uint32_t* s_flag) {
   for (;;) {
     __syncthreads();
@@ -439,19 +434,27 @@ __device__ __forceinline__ void run_inline_stages(KArgsC& a, DevSlot& s_slot, ui
       for (int q = 0; q < (int)(sizeof(Desc) / 4); ++q)
         dst[q] = __builtin_amdgcn_readfirstlane(src[q]);
     }
-    const uint32_t nt = desc_ntiles(d);
-    for (uint32_t tt = 0; tt < nt; ++tt) {
-      if (ld_dev(&a.sstate[d.slot].status) == CAF_OK) {
-        if (d.behavior == CAF_BHV_TANH)
-          tanh_tile(reinterpret_cast<const float*>(d.in0), reinterpret_cast<float*>(d.out),
-                    (uint64_t)d.p.s.rows * d.p.s.cols, tt);
-        else if (d.behavior == CAF_BHV_ROWSUM)
-          rowsum_tile(reinterpret_cast<const float*>(d.in0), reinterpret_cast<float*>(d.out),
-                      d.p.s.rows, d.p.s.cols, tt);
-        else if (threadIdx.x == 0)
-          st_dev(&a.sstate[d.slot].status, (int32_t)CAF_E_INVALID);
-      }
+    const float* in = reinterpret_cast<const float*>(d.in0);
+    if (d.behavior == CAF_BHV_TANH && d.hop_actor[0] >> 16 == CAF_BHV_ROWSUM &&
+        d.p.s.rows <= kInlineStageTiles * kRowsumTile) {
+      // tanh and then its row sums, both here: one pass, the tanh itself is
+      // nobody's reply.  The hop first: it asks whether the row actor lives.
       __syncthreads();
+      if (threadIdx.x == 0) *s_flag = stage_done(a, d, &s_slot) ? 1u : 0u;
+      __syncthreads();
+      if (!*s_flag) break;
+      const uint32_t* src = reinterpret_cast<const uint32_t*>(&s_slot.d);
+      uint32_t* dst = reinterpret_cast<uint32_t*>(&d);
+#pragma unroll
+      for (int q = 0; q < (int)(sizeof(Desc) / 4); ++q)
+        dst[q] = __builtin_amdgcn_readfirstlane(src[q]);
+      rowsum_range<kFull, true>(in, reinterpret_cast<float*>(d.out), d.p.s.rows, d.p.s.cols);
+    } else if (d.behavior == CAF_BHV_TANH) {
+      tanh_tile(d, 0, desc_ntiles(d));
+    } else if (d.behavior == CAF_BHV_ROWSUM) {
+      rowsum_tile<kFull>(d, 0, desc_ntiles(d));
+    } else if (threadIdx.x == 0) {
+      st_dev(&a.sstate[d.slot].status, (int32_t)CAF_E_INVALID);
     }
     wait_stores();
     __syncthreads();
@@ -1214,7 +1217,7 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
         __syncthreads();
         if (t == 0) s_cont = finish_tiles(a, d, ntiles, run, &s_slot) ? 1u : 0u;
         __syncthreads();
-        if (s_cont) run_inline_stages(a, s_slot, &s_cont);
+        if (s_cont) run_inline_stages<kFull>(a, s_slot, &s_cont);
         j += run;
       }
       last_work = now_ticks();

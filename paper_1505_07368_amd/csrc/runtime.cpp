@@ -705,6 +705,21 @@ uint32_t gemm_unit_for(const caf_gpu_system* s, uint32_t tiles, uint64_t ahead) 
   return u;
 }
 
+// Work tiles of an elementwise or row message.  A claim costs some
+// microseconds, as much as 16 KB take to stream, so a large matrix is cut into
+// about two tiles per workgroup (but tiles of at least 4096 elements, 16 KB of
+// rows, and at most 2^18 elements), a small one into the smallest.
+void stage_tiles(const caf_gpu_system* s, Desc* d) {
+  const uint64_t ne = (uint64_t)d->p.s.rows * d->p.s.cols;
+  const uint64_t per = ne / (2ull * s->grid_light);  // elements per tile
+  if (d->behavior == CAF_BHV_TANH) {
+    d->tcfg = (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, per / kTanhTile));
+  } else {
+    const uint64_t rows = std::max<uint64_t>(per, 4096) / d->p.s.cols;
+    d->tcfg = (uint32_t)std::min<uint64_t>(1u << 16, std::max<uint64_t>(4, rows / 4 * 4));
+  }
+}
+
 // Builds the descriptor of the first stage (all fields except slot, seq and
 // request id).
 void fill_desc(const caf_gpu_system* s, const ActorRec& a, uint32_t aidx, const void* args,
@@ -755,6 +770,7 @@ void fill_desc(const caf_gpu_system* s, const ActorRec& a, uint32_t aidx, const 
       const caf_shape_args* x = (const caf_shape_args*)args;
       d->p.s.rows = x->rows;
       d->p.s.cols = x->cols;
+      stage_tiles(s, d);
       break;
     }
     case CAF_BHV_HASHCHAIN:

@@ -1076,29 +1076,114 @@ __device__ __forceinline__ void gemm_bf16_tile_wide(const uint16_t* __restrict__
 // ---------------------------------------------------------------------------
 // Support behaviours (pipeline stages and ping-pong).
 // ---------------------------------------------------------------------------
-__device__ void tanh_tile(const float* __restrict__ x, float* __restrict__ y, uint64_t count,
-                          uint32_t tile) {
-  const uint64_t base = (uint64_t)tile * kTanhTile;
-#pragma unroll 4
-  for (uint32_t e = threadIdx.x; e < kTanhTile; e += kThreads) {
-    const uint64_t i = base + e;
-    if (i < count) store_reply(y + i, tanhf(x[i]));
+// A 16-byte write-through store (see store_reply) at byte `off` of the buffer
+// `r`: bits 0 and 4 of the cache policy are sc0 and sc1.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t reply_buffer(void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ void store_reply16(__amdgpu_buffer_rsrc_t r, uint32_t off, u32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, 17);
+}
+
+// Elements [base, base + len) of y = tanh(x), len <= 2^20.  HBM-bound: 16-byte
+// loads and stores, two of each in flight per thread (8192 x 4100 through
+// this and the row sums: 583 -> 284 us).
+__device__ __forceinline__ void tanh_range(const float* __restrict__ x, float* __restrict__ y,
+                                           uint64_t base, uint32_t len) {
+  const auto xg = global_ptr(x + base);
+  const auto yb = reply_buffer(y + base, len * 4u);
+  constexpr uint32_t U = 2, STEP = kThreads * 4;
+  const uint32_t whole = len / (U * STEP) * (U * STEP);
+  for (uint32_t e0 = threadIdx.x * 4; e0 < whole; e0 += U * STEP) {
+    f32x4u v[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u)
+      v[u] = *reinterpret_cast<const CAF_GLOBAL f32x4u*>(xg + e0 + u * STEP);
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      f32x4u r;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) r[c] = tanhf(v[u][c]);
+      store_reply16(yb, (e0 + u * STEP) * 4u, __builtin_bit_cast(u32x4, r));
+    }
+  }
+  for (uint32_t e = whole + threadIdx.x; e < len; e += kThreads)
+    store_reply(global_ptr(y + base) + e, tanhf(xg[e]));
+}
+
+// Row sums of the `rows` rows of `cols` columns at x (far fewer than 2^32: a
+// work tile's); kTanh: of the elements' tanh.  HBM-bound: 16-byte loads, R of them in flight per lane.  A
+// row belongs to as many lanes (a power of two) as have a vector of it, so
+// that short rows leave none idle (a chain's 128 x 128 matrix: 80 us as two
+// passes, one row at a time; 52 in one pass, a row per wave); a lane sums its
+// vectors in four chains, then the row's lanes meet in a tree.
+template <bool kTanh, uint32_t R>
+__device__ __forceinline__ void rowsum_rows(const float* __restrict__ x, float* __restrict__ y,
+                                            uint32_t rows, uint32_t cols) {
+  const uint32_t lane = lane_id();
+  const auto xg = global_ptr(x);
+  auto f = [](float v) { return kTanh ? tanhf(v) : v; };
+  uint32_t per = 64;  // lanes per row
+  while (per > 4 && per * 2 >= cols) per /= 2;
+  const uint32_t l = lane & (per - 1u), step = 64 / per, whole = cols & ~3u;
+  for (uint32_t rw = wave_id() * (R * step); rw < rows; rw += 4 * R * step) {
+    const uint32_t r = rw + lane / per;  // this lane's rows: r, r + step, ...
+    f32x4u s[R];
+#pragma unroll
+    for (uint32_t k = 0; k < R; ++k) s[k] = f32x4u{0.f, 0.f, 0.f, 0.f};
+    for (uint32_t c = l * 4; c < whole; c += per * 4) {
+      f32x4u v[R];
+#pragma unroll
+      for (uint32_t k = 0; k < R; ++k) {  // rows past the last: the last again
+        const uint64_t row = min(r + k * step, rows - 1u);
+        v[k] = *reinterpret_cast<const CAF_GLOBAL f32x4u*>(xg + row * cols + c);
+      }
+#pragma unroll
+      for (uint32_t k = 0; k < R; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[k][e] += f(v[k][e]);
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < R; ++k) {
+      const uint64_t row = min(r + k * step, rows - 1u);
+      float t = (s[k][0] + s[k][1]) + (s[k][2] + s[k][3]);
+      if (l < (cols & 3u)) t += f(xg[row * cols + whole + l]);
+      for (uint32_t off = per / 2; off > 0; off >>= 1) t += __shfl_xor(t, (int)off);
+      if (l == 0 && r + k * step < rows) store_reply(y + r + k * step, t);
+    }
   }
 }
 
-__device__ void rowsum_tile(const float* __restrict__ x, float* __restrict__ y, uint32_t rows,
-                            uint32_t cols, uint32_t tile) {
-  const uint32_t lane = lane_id(), w = wave_id();
-  for (uint32_t rr = w; rr < kRowsumTile; rr += 4) {
-    const uint32_t r = tile * kRowsumTile + rr;
-    if (r >= rows) break;
-    const float* row = x + (uint64_t)r * cols;
-    float s = 0.f;
-    for (uint32_t c = lane; c < cols; c += 64) s += row[c];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == 0) store_reply(y + r, s);
-  }
+// The row actor with four vectors in flight, as calls: the full variants have
+// the registers, but not in their drain loop.  The light variant inlines the
+// same with one: a call in it costs its escape-time tiles 7%.
+template <bool kTanh>
+__device__ __noinline__ void rowsum_rows_call(const float* x, float* y, uint32_t rows,
+                                              uint32_t cols) {
+  rowsum_rows<kTanh, 4>(x, y, rows, cols);
+}
+template <bool kFull, bool kTanh>
+__device__ __forceinline__ void rowsum_range(const float* x, float* y, uint32_t rows,
+                                             uint32_t cols) {
+  if constexpr (kFull) rowsum_rows_call<kTanh>(x, y, rows, cols);
+  else rowsum_rows<kTanh, 1>(x, y, rows, cols);
+}
+
+__device__ __forceinline__ void tanh_tile(const Desc& d, uint32_t tile, uint32_t count) {
+  const uint64_t ne = (uint64_t)d.p.s.rows * d.p.s.cols;
+  const uint32_t te = tanh_tile_elems(d);
+  const uint64_t base = (uint64_t)tile * te, end = base + (uint64_t)count * te;
+  for (uint64_t b = base; b < end && b < ne; b += te)
+    tanh_range(reinterpret_cast<const float*>(d.in0), reinterpret_cast<float*>(d.out), b,
+               (uint32_t)min((uint64_t)te, ne - b));
+}
+
+template <bool kFull>
+__device__ __forceinline__ void rowsum_tile(const Desc& d, uint32_t tile, uint32_t count) {
+  const uint32_t tr = rowsum_tile_rows(d), r0 = tile * tr, cols = d.p.s.cols;
+  const uint32_t rows = (uint32_t)min((uint64_t)count * tr, (uint64_t)(d.p.s.rows - r0));
+  rowsum_range<kFull, false>(reinterpret_cast<const float*>(d.in0) + (uint64_t)r0 * cols,
+                             reinterpret_cast<float*>(d.out) + r0, rows, cols);
 }
 
 __device__ void echo_tile(const Desc& d, uint8_t* inline_out) {

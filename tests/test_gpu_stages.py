@@ -1,0 +1,68 @@
+"""The elementwise and the row actor at the edges of their tiles (GPU).
+
+tanh: ROCm's tanhf, within 4 units in the last place.  Row sums: every order
+of summation is within (cols + 8) 2^-24 of the sum of magnitudes (as many
+roundings as additions); a chain's row sums of tanh add tanh's own 4 units.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 1), (1, 3), (3, 5), (1, 4096), (2, 4097), (5, 1023), (16, 256), (17, 255), (33, 4100),
+          (257, 64), (1000, 1), (4099, 513), (3, 300001)]
+ULP = 2.0 ** -23
+
+
+@pytest.fixture(scope="module", params=["batched", "plain"])
+def sysm(request):
+    from paper_1505_07368_amd import binding as cg
+    s = cg.System(mode=request.param, arena_bytes=256 << 20)
+    yield s
+    s.shutdown()
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+def test_shapes(sysm, offset):
+    """offset: the matrix starts that many floats into an allocation."""
+    import torch
+    from paper_1505_07368_amd import binding as cg
+    th, rs = sysm.spawn(cg.BHV_TANH), sysm.spawn(cg.BHV_ROWSUM)
+    fwd = sysm.spawn(cg.BHV_TANH, forward_to=rs)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    for rows, cols in SHAPES:
+        whole = torch.randn(rows * cols + offset, generator=g, device="cuda") * 2
+        x = whole[offset:]
+        out = torch.full((rows * cols + offset,), 7.0, device="cuda")[offset:]
+        torch.cuda.synchronize()
+        a = cg.caf_shape_args(rows, cols)
+        f = [sysm.request(th, a, inputs=[x], out=out), sysm.request(rs, a, inputs=[x]),
+             sysm.request(fwd, a, inputs=[x])]
+        got = [r.result() for r in f]
+        assert [st for st, _ in got] == [cg.OK] * 3, (rows, cols)
+        xd = x.double().view(rows, cols)
+        t = torch.tanh(xd)
+        assert ((out.double().view(rows, cols) - t).abs() <= 4 * ULP * t.abs()).all(), (rows, cols)
+        mag = xd.abs().sum(1)
+        assert ((got[1][1].double() - xd.sum(1)).abs() <= (cols + 8) * ULP / 2 * mag).all()
+        mag = t.abs().sum(1)
+        assert ((got[2][1].double() - t.sum(1)).abs() <= ((cols + 8) / 2 + 4) * ULP * mag).all()
+
+
+def test_fused_chain_asks_whether_the_row_actor_lives():
+    """A chain whose last actor quits while the messages wait is answered with
+    an error, also where its last two stages run as one."""
+    import torch
+    from paper_1505_07368_amd import binding as cg
+    with cg.System(mode="batched", arena_bytes=64 << 20) as s:
+        rs = s.spawn(cg.BHV_ROWSUM)
+        th = s.spawn(cg.BHV_TANH, forward_to=rs)
+        gm = s.spawn(cg.BHV_GEMM, forward_to=th)
+        A = torch.rand(64 * 64, device="cuda")
+        torch.cuda.synchronize()
+        assert s.hold(True) == cg.OK
+        f = [s.request(gm, cg.caf_gemm_args(64, cg.F32), inputs=[A, A]) for _ in range(3)]
+        s.quit(rs)
+        assert s.hold(False) == cg.OK
+        assert [r.result()[0] for r in f] == [cg.E_QUIT] * 3
