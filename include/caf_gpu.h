@@ -134,7 +134,8 @@ typedef struct {
                             0 = 200000 (persistent), 50 (batched) */
   int32_t grouping;      /* caf_grouping */
   uint32_t mandel_tile_px; /* pixels per Mandelbrot work tile (multiple of 256);
-                              0 = 512 (plain), 1024 (batched / persistent) */
+                              0 = 512 (plain), 1024 to 4096 by the message's
+                              cost and the load (batched / persistent) */
   uint32_t gemm_tile;      /* GEMM output tile edge (64 or 128) for every n, or 256 for
                               128 x 256 bf16 tiles; 0 = per class.  A 256 here or in
                               a class (ring modes, full_wgs_per_cu 2) gives them to

@@ -52,7 +52,10 @@ namespace {
 
 constexpr uint64_t kGranule = 256;
 constexpr uint32_t kMaxTemps = 6;
-constexpr uint32_t kPollBatch = 256;
+// Replies resolved per turn at the completion ring.  Short turns let a waiter
+// whose reply has come go on to its next request (4,096 tiles of 64 x 64 in a
+// window of 256: 1108 us at 256 replies a turn, 967 at 32).
+constexpr uint32_t kPollBatch = 32;
 
 inline int64_t now_ns() {
   return std::chrono::duration_cast<std::chrono::nanoseconds>(
@@ -705,6 +708,32 @@ uint32_t gemm_unit_for(const caf_gpu_system* s, uint32_t tiles, uint64_t ahead) 
   return u;
 }
 
+// Pixels per work tile of an escape-time message where the caller leaves the
+// choice: 1024, and twice or four times that where a tile is cheap next to its
+// claim (some microseconds, more with all workgroups claiming).  A tile may
+// have 1.7e6 pixel iterations (half as many in double) if the messages out
+// fill the grid with such tiles (1,024 tiles of 128 x 128 at max_iter 400
+// 1002 us with 1024, 649 with 4096; the image batch at 1000 1741 and 1887),
+// and 4.5e5 if they fill half of it (one 1920 x 1080 image at 120 139 us with
+// 1024, 114 with 2048; a 1021 x 773 one at 300 116 and 157), or an eighth
+// once 32 are out, or if 48 messages of at most 4096 pixels are (4,096 of
+// 64 x 64 at 100 in a window of 256 1159 and 1003; 180 of 67 x 67 at 267,
+// which this leaves at 1024, 121 and 163).
+uint32_t mandel_tile_for(const caf_gpu_system* s, const caf_mandel_args* m, uint64_t ahead) {
+  uint32_t t = s->mandel_tile_px;
+  if (s->cfg.mandel_tile_px || s->plain()) return t;
+  const uint64_t px = (uint64_t)m->rows * m->width, grid = s->grid_light;
+  const uint64_t iter = m->max_iter * (m->fp == CAF_F64 ? 2ull : 1ull);
+  const bool small = ahead >= 48 && px <= 4096;
+  for (; t < 4096; t *= 2) {
+    const uint64_t cost = 2 * t * iter, tiles = (ahead + 1) * px / (2 * t);
+    if (!(cost <= 1700000 && tiles >= grid) &&
+        !(cost <= 450000 && (small || tiles >= grid / (ahead >= 32 ? 8 : 2))))
+      break;
+  }
+  return t;
+}
+
 // Work tiles of an elementwise or row message.  A claim costs some
 // microseconds, as much as 16 KB take to stream, so a large matrix is cut into
 // about two tiles per workgroup (but tiles of at least 4096 elements, 16 KB of
@@ -747,7 +776,7 @@ void fill_desc(const caf_gpu_system* s, const ActorRec& a, uint32_t aidx, const 
       d->p.m64.row0 = m->row0;
       d->p.m64.rows = m->rows;
       d->p.m64.max_iter = m->max_iter;
-      d->tcfg = s->mandel_tile_px;
+      d->tcfg = mandel_tile_for(s, m, s->outstanding.load(std::memory_order_relaxed));
       if (a.spawn.palette_len) {
         d->flags |= DF_RGBA;
         d->in0 = (uint64_t)(uintptr_t)a.spawn.palette;

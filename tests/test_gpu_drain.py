@@ -38,3 +38,25 @@ def test_tile_map_by_one_thread_and_by_the_workgroup(cg, rows):
             got = img.cpu().numpy().reshape(r, 32)
             assert (got == ref).all(), (r, int((got != ref).sum()))
             f.release()
+
+
+@pytest.mark.parametrize("fp", ["f32", "f64"])
+@pytest.mark.parametrize("width,rows,max_iter", [(64, 64, 100), (67, 67, 110), (33, 125, 240),
+                                                 (1, 1, 9), (5, 4097, 50), (129, 130, 700)])
+def test_tiles_grow_with_the_load(cg, width, rows, max_iter, fp):
+    """Counts are exact at every work-tile size that the load at submission
+    chooses, from the first message (1024 pixels) to the last of many (4096
+    where a tile is cheap)."""
+    vp = gen.Viewport(-2.0, -1.25, 2.5 / width, 2.5 / rows, width, rows, max_iter)
+    ref = oracle.mandelbrot(vp.re_min, vp.im_min, vp.step_re, vp.step_im, width, 0, rows,
+                            max_iter, fp)
+    with cg.System(mode="batched", arena_bytes=256 << 20) as s:
+        a = s.spawn(cg.BHV_MANDELBROT)
+        assert s.hold(True) == cg.OK
+        args = cg.mandel_args(vp, fp=cg.F64 if fp == "f64" else cg.F32)
+        sent = [s.request(a, args) for _ in range(400)]
+        assert s.hold(False) == cg.OK
+        for f in sent:
+            st, img = f.result()
+            assert st == cg.OK and (img.cpu().numpy().reshape(rows, width) == ref).all()
+            f.release()
