@@ -52,10 +52,7 @@ namespace {
 
 constexpr uint64_t kGranule = 256;
 constexpr uint32_t kMaxTemps = 6;
-// Replies resolved per turn at the completion ring.  Short turns let a waiter
-// whose reply has come go on to its next request (4,096 tiles of 64 x 64 in a
-// window of 256: 1108 us at 256 replies a turn, 967 at 32).
-constexpr uint32_t kPollBatch = 32;
+constexpr uint32_t kPollBatch = 256;
 
 inline int64_t now_ns() {
   return std::chrono::duration_cast<std::chrono::nanoseconds>(
@@ -734,18 +731,23 @@ uint32_t mandel_tile_for(const caf_gpu_system* s, const caf_mandel_args* m, uint
   return t;
 }
 
-// Work tiles of an elementwise or row message.  A claim costs some
-// microseconds, as much as 16 KB take to stream, so a large matrix is cut into
-// about two tiles per workgroup (but tiles of at least 4096 elements, 16 KB of
-// rows, and at most 2^18 elements), a small one into the smallest.
+// Work tiles of an elementwise or row message.  While memory is busy a claim
+// waits for it too (its four dependent round trips took 34 us, a tile's own
+// work 25), so a large matrix is cut into one tile for half of the light
+// variant's workgroups, and two messages run side by side without a second
+// claim (8192 x 4100 through both actors: 286 us with four times as many
+// tiles, 219 with twice as many, 127 with these, 139 and 167 with two thirds
+// and half of them).  A small one is cut into the smallest tiles: 4096
+// elements, or four rows and at least 4096 elements of them.
 void stage_tiles(const caf_gpu_system* s, Desc* d) {
   const uint64_t ne = (uint64_t)d->p.s.rows * d->p.s.cols;
-  const uint64_t per = ne / (2ull * s->grid_light);  // elements per tile
+  const uint64_t half = std::max<uint64_t>(1, s->grid_light / 2);
+  const uint64_t per = std::max<uint64_t>(kTanhTile, (ne + half - 1) / half);  // elements per tile
   if (d->behavior == CAF_BHV_TANH) {
-    d->tcfg = (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, per / kTanhTile));
+    d->tcfg = (uint32_t)std::min<uint64_t>(64, (per + kTanhTile - 1) / kTanhTile);
   } else {
-    const uint64_t rows = std::max<uint64_t>(per, 4096) / d->p.s.cols;
-    d->tcfg = (uint32_t)std::min<uint64_t>(1u << 16, std::max<uint64_t>(4, rows / 4 * 4));
+    const uint64_t rows = (per + d->p.s.cols - 1) / d->p.s.cols;
+    d->tcfg = (uint32_t)std::min<uint64_t>(1u << 16, (rows + 3) / 4 * 4);
   }
 }
 

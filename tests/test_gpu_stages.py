@@ -66,3 +66,25 @@ def test_fused_chain_asks_whether_the_row_actor_lives():
         s.quit(rs)
         assert s.hold(False) == cg.OK
         assert [r.result()[0] for r in f] == [cg.E_QUIT] * 3
+
+
+@pytest.mark.parametrize("rows,cols", [(8191, 401), (5, 1048579), (2000003, 3), (4097, 4100)])
+def test_matrices_of_several_tiles_per_claim(sysm, rows, cols):
+    """Work tiles larger than the smallest: ragged last tiles, few long rows,
+    many short ones."""
+    import torch
+    from paper_1505_07368_amd import binding as cg
+    th, rs = sysm.spawn(cg.BHV_TANH), sysm.spawn(cg.BHV_ROWSUM)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    x = torch.randn(rows * cols, generator=g, device="cuda")
+    out = torch.full((rows * cols,), 7.0, device="cuda")
+    torch.cuda.synchronize()
+    a = cg.caf_shape_args(rows, cols)
+    f = [sysm.request(th, a, inputs=[x], out=out), sysm.request(rs, a, inputs=[x])]
+    got = [r.result() for r in f]
+    assert [st for st, _ in got] == [cg.OK] * 2
+    t = torch.tanh(x.double())
+    assert ((out.double() - t).abs() <= 4 * ULP * t.abs()).all()
+    xd = x.double().view(rows, cols)
+    assert ((got[1][1].double() - xd.sum(1)).abs() <= (cols + 8) * ULP / 2 * xd.abs().sum(1)).all()
