@@ -1110,7 +1110,12 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
       uint64_t pub = 0;
       const uint64_t rung = polls ? ld_dev(&bell->pub) : 0;
       if (c.next == c.end && (polls == 0 || (rung >> 1) > s_seen_cur)) {
-        const uint64_t pub0 = ld_dev(&a.dctl->tiles_pub);
+        // An idle workgroup takes the count its bell just gave: the line of
+        // the published count itself, read by all that wake, is one more
+        // queue (4,096 chains of 64 x 64 960 -> 700 us, 4,096 64 x 64 tiles
+        // in a window of 256 1100 -> 910; a workgroup that comes from work
+        // reads the count itself: with its bell instead 890 and 1140).
+        const uint64_t pub0 = polls ? rung >> 1 : ld_dev(&a.dctl->tiles_pub);
         const uint64_t cur0 = ld_dev(&a.dctl->tiles_claimed);
         s_seen_cur = cur0;
         // Drain ahead: while the mailbox holds more than one pass and the
