@@ -32,8 +32,8 @@
  * exception crosses the interface.  Errors that arise after a request was
  * accepted arrive as the reply status of its future.
  *
- * Threading: every call is thread-safe.  One host poller thread per system
- * resolves futures.
+ * Threading: every call is thread-safe.  Threads that wait for replies
+ * resolve them; one host poller thread per system does while nobody waits.
  */
 #ifndef CAF_GPU_H
 #define CAF_GPU_H
@@ -144,7 +144,9 @@ typedef struct {
                               edge */
   uint32_t gemm_tile_class[4]; /* the same choice for n <= 64, <= 128, <= 256, > 256;
                                   0 = default (64 up to n = 64, else 128; fp32 products
-                                  64 while the chip has room for more tiles) */
+                                  64 while the chip has room for more tiles; bf16
+                                  products that qualify 256 while the messages out
+                                  fill the grid with them) */
   uint32_t full_wgs_per_cu; /* drain workgroups per compute unit while a GEMM actor
                                exists: 0 or 2 = two (64-deep bf16 slices; suits
                                matrix-heavy loads), 3 = three (32-deep bf16

@@ -252,9 +252,9 @@ __host__ __device__ inline uint32_t desc_ntiles(const Desc& d) {
   }
 }
 
-// Completion notifications for one native driver: the poller thread pushes
-// the tag of each resolved tagged future, the driver pops (single producer,
-// single consumer).
+// Completion notifications for one native driver: whoever resolves a tagged
+// future (holding the completion ring) pushes its tag, the driver pops (one
+// producer at a time, one consumer).
 struct DriveQ {
   uint32_t* buf = nullptr;
   uint64_t mask = 0;
@@ -279,8 +279,8 @@ int offload_stage_setup(int device);
 
 }  // namespace cafgpu
 
-// Request entry used by the native driver: like caf_gpu_request, and the
-// poller pushes `tag` into `q` when the future resolves.  try_only: never
+// Request entry used by the native driver: like caf_gpu_request, and `tag` is
+// pushed into `q` when the future resolves.  try_only: never
 // wait for admission; a message that does not fit yet (mailbox or arena
 // full, but it would fit an empty arena) returns kTryLater and is not
 // counted as refused.

@@ -17,14 +17,16 @@
 //    batch (by behaviour, largest GEMMs first, or mailbox order), prefix-sums
 //    the per-message work-tile counts into one global tile sequence and
 //    publishes it (the drainer reserving first).  Every workgroup claims
-//    tiles of that sequence with a fetch_add on a claim cursor (see
+//    tiles of that sequence with a fetch_add on a claim cursor (idle ones
+//    poll copies of the published count, their bells; see
 //    "claiming work tiles" below), and no workgroup ever waits for one that
 //    may not be resident; consecutive claimed tiles of one GEMM (in work
 //    units of whole output tiles) run as one stream of k slices, those of one
 //    Mandelbrot message as one range of pixel blocks.  Stateful hash-chain entries are applied by the
 //    drainer itself, in mailbox order, while it holds the lock.  The
 //    workgroup finishing a message's last tile either publishes its reply
-//    (a completion record in host memory, released at system scope) or
+//    (a completion record in host memory; replies are stored write-through,
+//    so they are out before the record without a cache writeback) or
 //    forwards the reply to the next actor of a pipeline on the device (no
 //    host round trip): a stage of at most kInlineStageTiles tiles runs in
 //    that workgroup at once, a larger one is published as new work tiles.

@@ -3,8 +3,9 @@
 // The host side owns: the actor table (behaviour, signature, forwarding
 // target, alive flag), request ids and futures, the slot pool and the
 // arena sub-allocator that enforce the HBM budget (admission), the mailbox
-// ring writer, the drain-kernel launcher, and one poller thread that turns
-// completion records into resolved futures exactly once.
+// ring writer, the drain-kernel launcher, and what turns completion records
+// into resolved futures exactly once: the threads that wait for replies, and
+// one poller thread while nobody does.
 //
 // Paper correspondence: spawn_cl and the OpenCL actor (Sec. 4.6), typed
 // interfaces checked per message (Sec. 4.5), sync_send / then with unique
@@ -14,13 +15,13 @@
 // Concurrency: one mutex (`mu`) guards the actor table, the slot pool, the
 // arena and the ring writer; a request takes it once in the common case.
 // Resolving replies never takes it: finished slots go into a ring that only
-// the thread reading the completion ring appends to, unreferenced futures onto a lock-free stack, and each
-// later request returns a few of them to the slot pool, the future pool and
-// the arena (all of them when it would otherwise be refused).  A contended
-// mutex hand-off costs the poller a sleep and a wake-up per batch of
-// completions.  Fields written by the submitting side and by the poller sit
-// on separate cache lines, and the poller's view of a slot is kept apart
-// from the arena blocks only the submitting side reads.
+// the thread reading the completion ring appends to, unreferenced futures onto
+// a lock-free stack, and each later request returns a few of them to the slot
+// pool, the future pool and the arena (all of them when it would otherwise be
+// refused).  A contended mutex hand-off costs the resolving thread a sleep and
+// a wake-up per batch of completions.  Fields written by the submitting and by
+// the resolving side sit on separate cache lines, and the resolver's view of a
+// slot is kept apart from the arena blocks only the submitting side reads.
 #include <hip/hip_runtime.h>
 #include <immintrin.h>
 
@@ -201,7 +202,7 @@ struct caf_future {
   bool pooled = false;
 };
 
-// What the poller needs of a slot (written at submit, cleared by the poller;
+// What the resolver needs of a slot (written at submit, cleared by it;
 // one line per slot so neighbouring slots do not share it).
 struct alignas(64) SlotInfo {
   uint64_t req_id = 0;
@@ -243,7 +244,7 @@ struct caf_gpu_system {
   DevActor* dactors = nullptr;
   KArgs kargs{};
   uint32_t cap = 0;
-  // The submitting threads and the poller thread each write their own group
+  // The submitting threads and the resolving one each write their own group
   // of fields below; the groups, and every field both sides write, start on
   // their own 64-byte line, so a completion does not evict the submit
   // path's lines (the lock, the ring tail, the pools).
@@ -262,7 +263,7 @@ struct caf_gpu_system {
   bool shut = false;
   std::vector<uint32_t> pend_slots;        // retired, not yet returned (mu)
   std::vector<caf_future*> pend_futs;
-  // Finished slots: the poller appends (single producer), reclaim() takes
+  // Finished slots: the resolver appends (holding comp_lock), reclaim() takes
   // them in order under mu.  Every slot is in it at most once, so a power
   // of two >= the slot count never overflows.
   std::vector<uint32_t> retired_ring;
@@ -271,7 +272,7 @@ struct caf_gpu_system {
   // written by both sides
   alignas(64) std::atomic<uint64_t> outstanding{0};
   alignas(64) std::atomic<uint32_t> waiters{0};
-  alignas(64) std::atomic<uint64_t> retired_tail{0};  // poller
+  alignas(64) std::atomic<uint64_t> retired_tail{0};  // resolver
   // Returned without mu: pushed by any thread, emptied whole under mu.
   alignas(64) std::atomic<caf_future*> retired_futs{nullptr};
   // drain kernel
