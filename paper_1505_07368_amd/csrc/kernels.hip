@@ -1114,9 +1114,9 @@ __device__ __forceinline__ void drain_body(KArgsC& a) {
       if (c.next == c.end && (polls == 0 || (rung >> 1) > s_seen_cur)) {
         // An idle workgroup takes the count its bell just gave: the line of
         // the published count itself, read by all that wake, is one more
-        // queue (4,096 chains of 64 x 64 960 -> 700 us, 4,096 64 x 64 tiles
-        // in a window of 256 1100 -> 910; a workgroup that comes from work
-        // reads the count itself: with its bell instead 890 and 1140).
+        // queue (4,096 64 x 64 tiles in a window of 256 1100 -> 910 us).  A
+        // workgroup that comes from work reads the count itself, which its
+        // bell follows by a store (the same tiles with the bell: 1140 us).
         const uint64_t pub0 = polls ? rung >> 1 : ld_dev(&a.dctl->tiles_pub);
         const uint64_t cur0 = ld_dev(&a.dctl->tiles_claimed);
         s_seen_cur = cur0;
