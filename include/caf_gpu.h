@@ -151,7 +151,8 @@ typedef struct {
                                exists: 0 or 2 = two (64-deep bf16 slices; suits
                                matrix-heavy loads), 3 = three (32-deep bf16
                                slices; more waves for escape-time tiles mixed
-                               with products, slower matrix tiles) */
+                               with products, slower matrix tiles, and fp32
+                               products in 64-tiles whatever the tile choice) */
 } caf_gpu_config;
 
 /* Parameter blocks (the non-buffer part of a message), one per behaviour. */

@@ -402,9 +402,13 @@ __device__ __forceinline__ void run_tiles(KArgsC& a, const Desc& d, uint32_t til
         else
           gemm_bf16_tile<64, kBk>(A16, B16, C, d.p.g.n, t0, cnt, (lds_u8*)smem);
       } else {
-        constexpr int kNBuf = kBk == kBf16SliceK ? 2 : 1;  // the LDS of this variant
-        if (d.tcfg == 128) gemm_f32_tile<128, kNBuf>(A, B, C, d.p.g.n, t0, cnt, (lds_u8*)smem);
-        else gemm_f32_tile<64, kNBuf>(A, B, C, d.p.g.n, t0, cnt, (lds_u8*)smem);
+        // three workgroups per compute unit: half the LDS, and registers for
+        // the two accumulators of 64-tiles only (256 products of n = 512 in
+        // 128-tiles 3154 us, spilling; in 64-tiles 940)
+        constexpr bool kSmall = kBk != kBf16SliceK;
+        if (d.tcfg == 64) gemm_f32_tile<64, kSmall ? 1 : 2>(A, B, C, d.p.g.n, t0, cnt, (lds_u8*)smem);
+        else if constexpr (!kSmall) gemm_f32_tile<128>(A, B, C, d.p.g.n, t0, cnt, (lds_u8*)smem);
+        else if (threadIdx.x == 0) st_dev(&a.sstate[d.slot].status, (int32_t)CAF_E_DEVICE);
       }
       return;
     }

@@ -687,6 +687,7 @@ uint32_t gemm_tile_for(const caf_gpu_system* s, const caf_gemm_args* g, const ca
       if (in[i].on_device && ((uintptr_t)in[i].data & 15u) != 0) aligned = false;
     if (aligned) return 256;
   }
+  if (g->in_dtype == CAF_F32 && s->kargs.full_wgs == 3 && !s->plain()) return 64;  // see run_tiles
   if (asked) return asked == 256 ? 128u : asked;
   const bool idle = (ahead + 1) * e * e < s->grid_full / (ahead ? 8 : 3);
   return n <= 64 || (g->in_dtype == CAF_F32 && idle) ? 64u : 128u;
@@ -695,14 +696,17 @@ uint32_t gemm_tile_for(const caf_gpu_system* s, const caf_gemm_args* g, const ca
 // Output tiles per work unit of a product of `tiles` tiles.  A product that
 // one workgroup completes needs no shared count and its tiles run as one
 // stream of slices: four tiles per unit up to four tiles, two up to sixteen
-// (1,024 products of n = 256: fp32 402 -> 353 us, bf16 301 -> 218; 148 bf16
-// products of 512: 224 -> 179; larger ones gain nothing, and a single large
-// product would leave workgroups idle: n = 4096 in bf16 350 us in units of
-// four, 241 in single tiles).  Smaller while the units of all products
-// together do not fill an eighth of the grid.
-uint32_t gemm_unit_for(const caf_gpu_system* s, uint32_t tiles, uint64_t ahead) {
+// (1,024 bf16 products of n = 256: 301 -> 218 us, 148 of 512: 224 -> 179; 512
+// fp32 products of 17 to 500 543 -> 489; larger ones gain nothing, and a
+// single large product would leave workgroups idle: n = 4096 in bf16 350 us in
+// units of four, 241 in single tiles).  Smaller while the units of all
+// products together do not fill an eighth of the grid; fp32 tiles, which run
+// longer, are single until units of two fill all of it (16 products of
+// n = 512: 164 -> 112 us).
+uint32_t gemm_unit_for(const caf_gpu_system* s, uint32_t tiles, bool bf16, uint64_t ahead) {
   uint32_t u = tiles <= 4 ? 4u : tiles <= 16 ? 2u : 1u;
-  while (u > 1 && (ahead + 1) * ((tiles + u - 1) / u) < s->grid_full / 8) u /= 2;
+  while (u > 1 && (ahead + 1) * ((tiles + u - 1) / u) < s->grid_full / (bf16 || u == 4 ? 8 : 1))
+    u /= 2;
   return u;
 }
 
@@ -794,7 +798,7 @@ void fill_desc(const caf_gpu_system* s, const ActorRec& a, uint32_t aidx, const 
       // the messages ahead of this one; a launch per message has the chip to itself
       const uint64_t ahead = s->plain() ? 0 : s->outstanding.load(std::memory_order_relaxed);
       d->tcfg = gemm_tile_for(s, g, in, ahead);
-      d->p.g.unit = gemm_unit_for(s, gemm_tiles(*d), ahead);
+      d->p.g.unit = gemm_unit_for(s, gemm_tiles(*d), g->in_dtype == CAF_BF16, ahead);
       break;
     }
     case CAF_BHV_TANH:

@@ -303,17 +303,26 @@ __device__ __forceinline__ void store_c(CAF_GLOBAL float* C, uint32_t n, uint32_
 // fp32 inputs, on the bf16 matrix cores.  Each operand element is split into
 // three bf16 terms, a = a1 + a2 + a3: a1 = bf16(a), a2 = bf16(a - a1),
 // a3 = a - a1 - a2, which is exact (3 x 8 significant bits and the signs hold
-// fp32's 24), and a product is the six terms a1 b1, a1 b2, a2 b1, a2 b2,
-// a1 b3, a3 b1, each exact in fp32 and accumulated there (of the three left
-// out, a2 b3 and a3 b2 have a root mean square of 2^-26 of |a b|).  Six
-// 32x32x16 bf16 instructions (32 cycles each) replace eight 32x32x2 fp32 ones
-// (64 cycles each).  Against float64 the sums are no further off than the
-// fp32 instructions': they are rounded six times per 16 k instead of eight
-// times (relative error for entries U(-1, 1), fp32 instructions / split:
-// n = 64 1.4e-7 / 1.1e-7, 512 4.0e-7 / 3.4e-7, 1024 5.7e-7 / 4.8e-7).
-// Products in a batch, 1024 of n = 512: 3277 -> 2167 us (84 -> 127 TFLOP/s),
-// n = 4096: 109 -> 166; the clock drops to 1.7 GHz under this load, and the
-// rate of the bf16 instructions there, a sixth of 1.3 PFLOP/s, bounds it.
+// fp32's 24; the split is Dekker's idea with bf16 parts, as in Henry, Tang
+// and Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
+// Higher-Precision Computations", ARITH 2019).  A product is then nine terms,
+// each exact in fp32.  a1 b1 has an accumulator of its own and seven more
+// share a second one, whose roundings are 2^-8 as large; a3 b3, at most
+// 2^-36 |a b|, is left out: less than those roundings.  Eight 32x32x16 bf16
+// instructions (32 cycles each) replace eight 32x32x2 fp32 ones (64 cycles).
+//
+// Errors against float64, in 2^-24 of the sum of |a b|, root mean square,
+// fp32 instructions / this: entries U(-1, 1) 0.40 / 0.11 at n = 512, U(0, 1)
+// 5.1 / 1.9, magnitudes spread over 2^-20 .. 2^20 0.95 / 0.83 at n = 33 and
+// 1.9 / 1.4 at 512; sums of one term (a diagonal factor) 0.42 / 0.42, at most
+// 0.500 / 0.506 of the last place.  Up to n = 32 the bf16 instruction's own
+// sum of 16 products could be the larger (magnitudes over 2^-10 .. 2^10, n = 4:
+// 0.39 / 0.58), and those products are one block: they take the fp32
+// instructions.
+// Products in a batch, 256 of n = 512: 815 us with the fp32 instructions,
+// 650 us (106 TFLOP/s); 4,096 of 64 .. 512 3455 -> 2800.  The matrix
+// instructions bound it: the clock drops to 1.7 GHz under them, and an eighth
+// of the 1.3 PFLOP/s that large bf16 products reach is 163 TFLOP/s.
 //
 // The split is exact only while no term underflows, and a value near the top
 // of the range rounds to infinity.  So a tile is redone with the fp32
@@ -330,16 +339,17 @@ __device__ __forceinline__ void store_c(CAF_GLOBAL float* C, uint32_t n, uint32_
 // conversion, which also transposes B.  Registers hold the next two slices,
 // so a load has two slices of matrix work to arrive in.
 //
-// Any n >= 4 and any alignment of floats: 16-byte loads, from addresses
+// Any n > 32 and any alignment of floats: 16-byte loads, from addresses
 // clamped into the matrix, put right in the last slice of a tile where n is
-// no multiple of the slice depth (512 products of n = 17 .. 500: 1316 ->
-// 486 us; element loads before).
+// no multiple of the slice depth (512 products of n = 17 .. 500: 1316 us with
+// element loads and fp32 instructions, 489).
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // One 32 x 32 block of C by one wave with the fp32 matrix instructions,
-// operands straight from memory: n < 4 and the tiles described above.
+// operands straight from memory: products of n <= 32 and the tiles described
+// above.
 __device__ __noinline__ void gemm_f32_direct(const float* A, const float* B, float* C, uint32_t n,
                                              uint32_t row0, uint32_t col0) {
   const auto Ag = global_ptr(A);
@@ -375,7 +385,8 @@ constexpr uint32_t kF32BufBytes = 36864;
 // those that load B differ in how they split and store a slice, and each has
 // its own copy of the loop, so that a step is one basic block in which the
 // split's vector instructions are scheduled between the matrix instructions
-// (a 32-cycle matrix instruction leaves seven vector issue slots).
+// (a 32-cycle matrix instruction leaves seven vector issue slots; the split
+// takes five of them).
 template <int TE, int NBUF, bool kA>
 __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
                                                 const float* __restrict__ B,
@@ -396,14 +407,14 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
   const uint32_t wm = w >> 1, wn = w & 1;
   const uint32_t tt = t & 127u;
 
-  floatx16 acc[WB][WB];
+  floatx16 acc[WB][WB], low[WB][WB];  // a1 b1, and the other terms
   auto zero_acc = [&]() {
 #pragma unroll
     for (uint32_t i = 0; i < WB; ++i)
 #pragma unroll
       for (uint32_t j = 0; j < WB; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = low[i][j][r] = 0.f;
   };
   zero_acc();
 
@@ -523,28 +534,31 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
     for (uint32_t sub = 0; sub < SUB; ++sub) {
       const lds_u8* As = buf + sub * (2 * OPND) + (lane >> 5) * 16;
       const lds_u8* Bs = As + OPND;
-      bf16x8 a[3][WB], b[3][WB];
+      bf16x8 a[3][WB], b[WB];
 #pragma unroll
       for (uint32_t p = 0; p < 3; ++p)
 #pragma unroll
-        for (uint32_t i = 0; i < WB; ++i) {
+        for (uint32_t i = 0; i < WB; ++i)
           a[p][i] = __builtin_bit_cast(
               bf16x8, *reinterpret_cast<const CAF_LDS u32x4*>(
                           As + p * PLANE + (wm * (TE / 2) + i * 32 + (lane & 31)) * ROW));
-          b[p][i] = __builtin_bit_cast(
+#pragma unroll
+      for (int pb = 2; pb >= 0; --pb) {
+#pragma unroll
+        for (uint32_t j = 0; j < WB; ++j)
+          b[j] = __builtin_bit_cast(
               bf16x8, *reinterpret_cast<const CAF_LDS u32x4*>(
-                          Bs + p * PLANE + (wn * (TE / 2) + i * 32 + (lane & 31)) * ROW));
-        }
-      // the small terms first
-      constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+                          Bs + pb * PLANE + (wn * (TE / 2) + j * 32 + (lane & 31)) * ROW));
 #pragma unroll
-      for (int q = 0; q < 6; ++q)
+        for (int pa = pb == 2 ? 1 : 2; pa >= 0; --pa)  // all but a3 b3
 #pragma unroll
-        for (uint32_t i = 0; i < WB; ++i)
+          for (uint32_t i = 0; i < WB; ++i)
 #pragma unroll
-          for (uint32_t j = 0; j < WB; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]][i], b[PB[q]][j],
-                                                                acc[i][j], 0, 0, 0);
+            for (uint32_t j = 0; j < WB; ++j) {
+              floatx16& to = pa + pb ? low[i][j] : acc[i][j];
+              to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pa][i], b[j], to, 0, 0, 0);
+            }
+      }
     }
   };
   // Stores the tile, or has it redone where the split does not hold.
@@ -560,7 +574,10 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
 #pragma unroll
       for (uint32_t j = 0; j < WB; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) big[r & 3] = __builtin_fmaf(acc[i][j][r], 0.f, big[r & 3]);
+        for (int r = 0; r < 16; ++r) {
+          acc[i][j][r] += low[i][j][r];
+          big[r & 3] = __builtin_fmaf(acc[i][j][r], 0.f, big[r & 3]);
+        }
     const float any = (big[0] + big[1]) + (big[2] + big[3]);
     redo = __builtin_amdgcn_ballot_w64(redo || !(any == 0.f)) != 0;
     const uint32_t r0 = tm * TE + wm * (TE / 2), c0 = tn * TE + wn * (TE / 2);
@@ -615,10 +632,10 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
       // matrix instructions with the split between them
       __builtin_amdgcn_sched_group_barrier(0x100, 4 * WB, 0);  // fragments first
 #pragma unroll
-      for (uint32_t q = 0; q < 6 * SUB * WB * WB; ++q) {
+      for (uint32_t q = 0; q < 8 * SUB * WB * WB; ++q) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
         __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
       }
     }
@@ -654,7 +671,7 @@ __device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A,
   CAF_LDS uint32_t(*s_min)[2] =
       reinterpret_cast<CAF_LDS uint32_t(*)[2]>(smem + NBUF * kF32BufBytes);
   const uint32_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(wave_id());
-  if (n < 4) {  // one tile
+  if (n <= 32) {  // one block
     if (w == 0) gemm_f32_direct(A, B, C, n, 0, 0);
     __syncthreads();
     return;

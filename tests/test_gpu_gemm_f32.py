@@ -81,3 +81,38 @@ def test_infinities_and_nans_stay_in_their_rows_and_columns(sysm, n):
     assert ((np.isinf(C) == np.isinf(R)) | near).all()
     ok = np.isfinite(R) & ~near
     assert np.allclose(C[ok], R[ok], rtol=(n + 8) * 2.0 ** -24, atol=0)
+
+
+@pytest.mark.parametrize("n", [5, 32, 33, 64, 130, 257])
+@pytest.mark.parametrize("at", [0, 100])
+def test_sums_of_one_term_are_rounded_once(sysm, n, at):
+    """A diagonal factor: each output is one product.  Its largest part is
+    exact; what is added to it has at most eight roundings of 2^-24 of 2^-8 of
+    the product, 2^-5 of the last place, and the sum rounds once more.  at:
+    the factor's magnitudes are from 2^-109 on, where its last bits are
+    numbers smaller than the smallest normal one."""
+    g = np.random.Generator(np.random.PCG64(n))
+    A = np.diag(g.uniform(1, 2, n) * 2.0 ** (-109 if at else 0)).astype(np.float32)
+    B = (g.uniform(1, 2, (n, n)) * np.exp2(g.integers(-4, 4, (n, n)) + (60 if at else 0)))
+    B = B.astype(np.float32)
+    C = _product(sysm, A, B).astype(np.float64)
+    R = A.astype(np.float64) @ B.astype(np.float64)
+    ulp = np.exp2(np.floor(np.log2(np.abs(R))) - 23)
+    assert (np.abs(C - R) <= (0.5 + 2.0 ** -5) * ulp).all(), float((np.abs(C - R) / ulp).max())
+
+
+@pytest.mark.parametrize("n", [65, 129, 257])
+def test_spread_magnitudes_are_no_further_off_than_one_rounding_per_term(sysm, n):
+    """Magnitudes from 2^-20 to 2^20: the root mean square error is at most
+    that of a fused multiply-add per term, in fp32."""
+    g = np.random.Generator(np.random.PCG64(n))
+    A, B = ((g.standard_normal((n, n)) * np.exp2(g.uniform(-20, 20, (n, n)))).astype(np.float32)
+            for _ in range(2))
+    C = _product(sysm, A, B).astype(np.float64)
+    A, B = A.astype(np.float64), B.astype(np.float64)
+    chain = np.zeros((n, n), np.float32)
+    for k in range(n):
+        chain = (chain + np.outer(A[:, k], B[k])).astype(np.float32)
+    R, size = A @ B, np.abs(A) @ np.abs(B)
+    rms = lambda x: float(np.sqrt((((x - R) / size) ** 2).mean()))
+    assert rms(C) <= rms(chain.astype(np.float64)), (rms(C), rms(chain.astype(np.float64)))
