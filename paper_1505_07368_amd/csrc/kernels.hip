@@ -309,12 +309,12 @@ __device__ __forceinline__ void hash_step(KArgsC& a, const Desc& d) {
 // LDS of a full variant: the largest work tile, two buffers of a bf16 GEMM
 // slice at TE = 128, for slices of bk (with 64-deep slices it also holds
 // the three stages of a wide bf16 tile and the fp32 tile's two buffers; 32-deep
-// slices, one of those buffers), plus the fp32 tile's minima.  The light
+// slices, one of those buffers), plus the fp32 tile's notes.  The light
 // variant only needs the drain scratch.
-constexpr uint32_t smem_bytes(int bk) { return 2 * (2 * 128 * (bk + 8) * 2) + 32; }
+constexpr uint32_t smem_bytes(int bk) { return 2 * (2 * 128 * (bk + 8) * 2) + kF32NoteBytes; }
 static_assert(smem_bytes(kBf16SliceK) >= kWideSmemBytes, "wide bf16 tiles fit the full LDS");
-static_assert(smem_bytes(kBf16SliceK) >= 2 * kF32BufBytes + 24 &&
-                  smem_bytes(32) >= kF32BufBytes + 24,
+static_assert(smem_bytes(kBf16SliceK) >= 2 * kF32BufBytes + kF32NoteBytes &&
+                  smem_bytes(32) >= kF32BufBytes + kF32NoteBytes,
               "fp32 tiles fit");
 
 // The square matrix tiles as calls, for the drain's full variant: inlined next

@@ -325,11 +325,18 @@ __device__ __forceinline__ void store_c(CAF_GLOBAL float* C, uint32_t n, uint32_
 // of the 1.3 PFLOP/s that large bf16 products reach is 163 TFLOP/s.
 //
 // The split is exact only while no term underflows, and a value near the top
-// of the range rounds to infinity.  So a tile is redone with the fp32
-// instructions (gemm_f32_direct) if the smallest non-zero magnitudes of its A
-// rows and B columns are below 2^-103, or their product below 2^-100, or if
-// an output is not finite: infinities, NaNs, tiny and huge inputs come out as
-// those instructions give them.
+// of the range rounds to infinity.  So a 32 x 32 block of C is redone with
+// the fp32 instructions (gemm_f32_direct) if an output in it is not finite,
+// or if its operands hold numbers so small that bits may have been lost
+// (F32Note) and one of its outputs is so small that these bits could show.
+// Infinities, NaNs, tiny and huge inputs come out as those instructions give
+// them; a softmax or a Gaussian kernel matrix, which holds tiny numbers next
+// to ordinary ones, is not redone (128 products of n = 512: 390 us as for
+// U(-1, 1) entries, 1525 us when every 128-tile with a product of entries
+// below 2^-100 was redone).  Where every output is about as small as fp32
+// holds (1e-33) the whole product is: 885 us, 475 with fp32 instructions only.
+// What is noted does not depend on the tile edge, nor does any sum: the same
+// product has the same bits whatever the load chose.
 //
 // Layout.  K advances in slices of 16 (TE = 128) or 2 x 16 (TE = 64), which
 // two waves load as A and two as B, 16 elements per thread.  LDS holds, per
@@ -341,43 +348,75 @@ __device__ __forceinline__ void store_c(CAF_GLOBAL float* C, uint32_t n, uint32_
 //
 // Any n > 32 and any alignment of floats: 16-byte loads, from addresses
 // clamped into the matrix, put right in the last slice of a tile where n is
-// no multiple of the slice depth (512 products of n = 17 .. 500: 1316 us with
-// element loads and fp32 instructions, 489).
+// no multiple of the slice depth and at the matrix's edges (512 products of
+// n = 17 .. 500: 1316 us with element loads and fp32 instructions, 489).
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // One 32 x 32 block of C by one wave with the fp32 matrix instructions,
-// operands straight from memory: products of n <= 32 and the tiles described
-// above.
+// operands straight from memory: products of n <= 32 and the blocks described
+// above.  16 k at a time, the lower half of the wave the first eight of them
+// and the upper half the others, loaded one step ahead.
 __device__ __noinline__ void gemm_f32_direct(const float* A, const float* B, float* C, uint32_t n,
                                              uint32_t row0, uint32_t col0) {
   const auto Ag = global_ptr(A);
   const auto Bg = global_ptr(B);
-  const uint32_t lane = lane_id(), kl = lane >> 5;
+  const uint32_t lane = lane_id(), kl = (lane >> 5) * 8;
   const uint32_t row = min(row0 + (lane & 31), n - 1u), col = min(col0 + (lane & 31), n - 1u);
+  const auto Ar = Ag + row * n + kl;
+  const auto Bc = Bg + kl * n + col;
   floatx16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  for (uint32_t k0 = 0; k0 < n; k0 += 16) {
-    float a[8], b[8];
+  const uint32_t whole = n / 16;  // steps of 16 k inside the matrix
+  f32x4u a[2], an[2];
+  float b[8], bn[8];
+  auto load = [&](uint32_t k0) {
+    an[0] = *reinterpret_cast<const CAF_GLOBAL f32x4u*>(Ar + k0);
+    an[1] = *reinterpret_cast<const CAF_GLOBAL f32x4u*>(Ar + k0 + 4);
 #pragma unroll
-    for (uint32_t q = 0; q < 8; ++q) {
-      const uint32_t k = k0 + 2 * q + kl, kc = min(k, n - 1u);
-      a[q] = Ag[(uint64_t)row * n + kc];
-      b[q] = Bg[(uint64_t)kc * n + col];
-      if (k >= n) a[q] = b[q] = 0.f;
-    }
+    for (uint32_t q = 0; q < 8; ++q) bn[q] = Bc[(k0 + q) * n];
+  };
+  auto multiply = [&]() {
 #pragma unroll
     for (uint32_t q = 0; q < 8; ++q)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q >> 2][q & 3], b[q], acc, 0, 0, 0);
+  };
+  if (whole) load(0);
+  for (uint32_t s = 0; s < whole; ++s) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) a[q] = an[q];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) b[q] = bn[q];
+    if (s + 1 < whole) load((s + 1) * 16);
+    multiply();
+  }
+  if (n % 16) {
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q) {
+      const uint32_t k = whole * 16 + kl + q, kc = min(k, n - 1u);
+      a[q >> 2][q & 3] = k < n ? Ag[row * n + kc] : 0.f;
+      b[q] = k < n ? Bg[kc * n + col] : 0.f;
+    }
+    multiply();
   }
   store_c<32>(global_ptr(C), n, row0, col0, acc);
 }
 
-// The exponents (biased) below which a tile's split may lose bits.
-constexpr uint32_t kSplitMinExp = 127 - 103;
+// Where the split may lose bits (biased exponents): an element below 2^-110
+// has bits below the smallest bf16 number, 2^-133, and a product below 2^-100
+// may have some below the smallest fp32 one.
+constexpr uint32_t kSplitMinExp = 127 - 110;
 constexpr uint32_t kSplitMinExpSum = 2 * 127 - 100;
+
+// What a tile notes of its operands, per 64 rows of A and 64 columns of B:
+// the smallest exponent of a non-zero element (255: all are zero), and 255
+// minus the largest.
+struct F32Note {
+  uint32_t a[2][2], b[2][2];
+};
+constexpr uint32_t kF32NoteBytes = 3 * sizeof(F32Note);
 
 constexpr uint32_t kF32BufBytes = 36864;
 
@@ -392,7 +431,7 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
                                                 const float* __restrict__ B,
                                                 float* __restrict__ C, uint32_t n, uint32_t tile0,
                                                 uint32_t count, lds_u8* lds,
-                                                CAF_LDS uint32_t (*s_min)[2]) {
+                                                CAF_LDS F32Note* s_note) {
   constexpr uint32_t WB = TE / 64;           // 32 x 32 blocks per wave and dimension
   constexpr uint32_t SUB = 128 / TE;         // 16 deep sub-slices per slice
   constexpr uint32_t KS = 16 * SUB;          // k per slice
@@ -407,7 +446,7 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
   const uint32_t wm = w >> 1, wn = w & 1;
   const uint32_t tt = t & 127u;
 
-  floatx16 acc[WB][WB], low[WB][WB];  // a1 b1, and the other terms
+  floatx16 acc[WB][WB], low[WB][WB];  // a1 b1, and the other eight terms
   auto zero_acc = [&]() {
 #pragma unroll
     for (uint32_t i = 0; i < WB; ++i)
@@ -426,8 +465,8 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
   const uint32_t b_k = (tt & 3u) * 4 + (tt / TE) * 16, b_col = ((tt % TE) >> 2) * 4;
   // Element offsets of its four 16-byte loads, clamped to the matrix's last
   // four elements: a load past the end of a row reads the next row's first
-  // elements, one past the matrix its last ones.  Rows and columns beyond n
-  // only feed outputs that are not stored; k beyond n is put right by fix().
+  // elements, one past the matrix its last ones.  fix() and edge() put right
+  // what lies beyond n.
   const uint32_t last4 = n * n - 4u;
   const uint32_t stride = kA ? (TE / 4) * n : n;  // between the four loads
   const uint32_t kstep = kA ? KS : KS * n;        // between slices
@@ -490,11 +529,37 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
       }
     }
   };
-  uint32_t vmin = 0xFFFFFFFFu;  // smallest (bits << 1) - 1 of this thread's elements of the tile
-  auto seen = [&](float x) { return (__builtin_bit_cast(uint32_t, x) << 1) - 1u; };
+  // Rows of A and columns of B outside the matrix, in tiles at its edge, are
+  // zero: they neither feed an output nor are noted.
+  auto edge = [&](Slice& s, uint32_t tm, uint32_t tn) {
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      if constexpr (kA) {
+        if (tm * TE + a_row + q * (TE / 4) >= n) s.v[q] = f32x4u{0.f, 0.f, 0.f, 0.f};
+      } else {
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e)
+          if (tn * TE + b_col + e >= n) s.v[q][e] = 0.f;
+      }
+    }
+  };
+  // Smallest non-zero and largest magnitude of this thread's elements of the
+  // tile, as bits << 1, the former less one.  A: per 64 rows.
+  constexpr int NOTES = kA ? (int)WB : 1;
+  uint32_t vmin[NOTES], vmax[NOTES];
+  auto clear_note = [&]() {
+#pragma unroll
+    for (int q = 0; q < NOTES; ++q) {
+      vmin[q] = 0xFFFFFFFFu;
+      vmax[q] = 0;
+    }
+  };
+  clear_note();
   // two consecutive k of one row or column -> a packed pair of each term
-  auto split = [&](float x, float y, uint32_t (&p)[3]) {
-    vmin = min(vmin, min(seen(x), seen(y)));
+  auto split = [&](float x, float y, int half, uint32_t (&p)[3]) {
+    const uint32_t mx = __builtin_bit_cast(uint32_t, x) << 1, my = __builtin_bit_cast(uint32_t, y) << 1;
+    vmin[half] = min(vmin[half], min(mx - 1u, my - 1u));
+    vmax[half] = max(vmax[half], max(mx, my));
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const f32x2 xy = {x, y};
@@ -513,21 +578,33 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
 #pragma unroll
     for (uint32_t q = 0; q < 4; ++q) {  // row q of A, column q of B
       uint32_t lo[3], hi[3];
-      split(kA ? s.v[q][0] : s.v[0][q], kA ? s.v[q][1] : s.v[1][q], lo);
-      split(kA ? s.v[q][2] : s.v[2][q], kA ? s.v[q][3] : s.v[3][q], hi);
+      const int half = kA ? (int)(q * WB / 4) : 0;
+      split(kA ? s.v[q][0] : s.v[0][q], kA ? s.v[q][1] : s.v[1][q], half, lo);
+      split(kA ? s.v[q][2] : s.v[2][q], kA ? s.v[q][3] : s.v[3][q], half, hi);
 #pragma unroll
       for (uint32_t p = 0; p < 3; ++p)
         *reinterpret_cast<CAF_LDS u32x2*>(dst + p * PLANE + q * (kA ? TE / 4 : 1) * ROW) =
             u32x2{lo[p], hi[p]};
     }
   };
-  auto note_min = [&](uint32_t tseq) {  // the tile's last slice is in LDS
+  auto note = [&](uint32_t tseq) {  // the tile's last slice is in LDS
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) vmin = min(vmin, (uint32_t)__shfl_xor((int)vmin, off));
-    if (lane == 0)
-      __hip_atomic_fetch_min(&s_min[tseq % 3][kA ? 0 : 1], vmin, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_WORKGROUP);
-    vmin = 0xFFFFFFFFu;
+    for (int q = 0; q < NOTES; ++q) {
+      uint32_t v = vmin[q] >> 24 | (255u - (vmax[q] >> 24)) << 16;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1)
+        v = __builtin_bit_cast(
+            uint32_t, __builtin_elementwise_min(
+                          __builtin_bit_cast(u16x2, v),
+                          __builtin_bit_cast(u16x2, (uint32_t)__shfl_xor((int)v, off))));
+      if (lane == 0) {
+        CAF_LDS uint32_t* to = kA ? s_note[tseq % 3].a[q] : s_note[tseq % 3].b[tt / 64 * WB / 2];
+        __hip_atomic_fetch_min(to, v & 0xFFFFu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_min(to + 1, v >> 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    clear_note();
   };
   auto mfma_slice = [&](const lds_u8* buf) {
 #pragma unroll
@@ -561,40 +638,69 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
       }
     }
   };
-  // Stores the tile, or has it redone where the split does not hold.
+  // Stores the tile; has the 32 x 32 blocks redone for which the split does
+  // not hold.
   auto finish_tile = [&](uint32_t tm, uint32_t tn, uint32_t tseq) {
-    const uint32_t ma = s_min[tseq % 3][0], mb = s_min[tseq % 3][1];
-    const uint32_t ea = (ma + 1u) >> 24, eb = (mb + 1u) >> 24;
-    // an operand of zeros only (0xFFFFFFFF) is exact
-    bool redo = ma != 0xFFFFFFFFu && mb != 0xFFFFFFFFu &&
-                (ea < kSplitMinExp || eb < kSplitMinExp || ea + eb < kSplitMinExpSum);
-    float big[4] = {0.f, 0.f, 0.f, 0.f};  // NaN if an output is not finite
+    const CAF_LDS F32Note& nt = s_note[tseq % 3];
+    const uint32_t ha = TE == 128 ? wm : 0u, hb = TE == 128 ? wn : 0u;
+    const uint32_t ea = __builtin_amdgcn_readfirstlane(nt.a[ha][0]),
+                   eb = __builtin_amdgcn_readfirstlane(nt.b[hb][0]);
+    // an operand of zeros only (255) is exact
+    const bool lossy = ea != 255u && eb != 255u &&
+                       (ea < kSplitMinExp || eb < kSplitMinExp || ea + eb < kSplitMinExpSum);
+    const uint32_t r0 = tm * TE + wm * (TE / 2), c0 = tn * TE + wn * (TE / 2);
+    uint32_t redo = 0;  // bit per block
+#pragma unroll
+    for (uint32_t i = 0; i < WB; ++i)
+#pragma unroll
+      for (uint32_t j = 0; j < WB; ++j) {
+        float any[2] = {0.f, 0.f};  // NaN if an output is not finite
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          acc[i][j][r] += low[i][j][r];
+          any[r & 1] = __builtin_fmaf(acc[i][j][r], 0.f, any[r & 1]);
+        }
+        if (__builtin_amdgcn_ballot_w64(!(any[0] + any[1] == 0.f))) redo |= 1u << (i * WB + j);
+      }
+    if (__builtin_expect(lossy, 0)) {
+      // 2^24 times what the split may have lost of an output: n 2^-134 of
+      // the other operand's largest for small elements, and n 2^-146
+      auto largest = [](uint32_t inv) {  // 2^(exponent + 1) of the biased one, finite
+        return __builtin_bit_cast(float, min(255u - inv + 1u, 254u) << 23);
+      };
+      const float ma = largest(__builtin_amdgcn_readfirstlane(nt.a[ha][1])),
+                  mb = largest(__builtin_amdgcn_readfirstlane(nt.b[hb][1]));
+      const float lost = (float)n * (0x1p-110f * ((ea < kSplitMinExp ? mb : 0.f) +
+                                                  (eb < kSplitMinExp ? ma : 0.f)) + 0x1p-122f);
+#pragma unroll
+      for (uint32_t i = 0; i < WB; ++i)
+#pragma unroll
+        for (uint32_t j = 0; j < WB; ++j) {
+          bool small = false;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const uint32_t row = r0 + i * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r & 3);
+            small |= row < n && __builtin_fabsf(acc[i][j][r]) < lost;
+          }
+          if (__builtin_amdgcn_ballot_w64(small && c0 + j * 32 + (lane & 31) < n))
+            redo |= 1u << (i * WB + j);
+        }
+    }
 #pragma unroll
     for (uint32_t i = 0; i < WB; ++i)
 #pragma unroll
       for (uint32_t j = 0; j < WB; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          acc[i][j][r] += low[i][j][r];
-          big[r & 3] = __builtin_fmaf(acc[i][j][r], 0.f, big[r & 3]);
-        }
-    const float any = (big[0] + big[1]) + (big[2] + big[3]);
-    redo = __builtin_amdgcn_ballot_w64(redo || !(any == 0.f)) != 0;
-    const uint32_t r0 = tm * TE + wm * (TE / 2), c0 = tn * TE + wn * (TE / 2);
-    if (__builtin_expect(redo, 0)) {
-      for (uint32_t i = 0; i < WB; ++i)
-        for (uint32_t j = 0; j < WB; ++j)
-          if (r0 + i * 32 < n && c0 + j * 32 < n)
-            gemm_f32_direct(A, B, C, n, r0 + i * 32, c0 + j * 32);
-    } else {
-#pragma unroll
-      for (uint32_t i = 0; i < WB; ++i)
-#pragma unroll
-        for (uint32_t j = 0; j < WB; ++j)
+        if (!(redo >> (i * WB + j) & 1u))
           store_c<TE>(Cg, n, r0 + i * 32, c0 + j * 32, acc[i][j]);
+    while (__builtin_expect(redo != 0, 0)) {
+      const uint32_t q = __builtin_ctz(redo);
+      redo &= redo - 1u;
+      const uint32_t rq = r0 + q / WB * 32, cq = c0 + q % WB * 32;
+      if (rq < n && cq < n) gemm_f32_direct(A, B, C, n, rq, cq);
     }
     zero_acc();
-    if (t < 2) s_min[(tseq + 2) % 3][t] = 0xFFFFFFFFu;
+    if (t < sizeof(F32Note) / 4)
+      reinterpret_cast<CAF_LDS uint32_t*>(s_note + (tseq + 2) % 3)[t] = 255u;
   };
 
   Slice s0, s1;
@@ -606,9 +712,13 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
   load_next(1);
   load(s1);  // with a single slice, that slice again
   load_next(2);
-  if (ragged && nk == 1) fix(s0, stm, stn);
+  auto put_right = [&](Slice& s, uint32_t k) {  // slice k of tile (stm, stn)
+    if (ragged && k == nk - 1) fix(s, stm, stn);
+    if ((kA ? stm : stn) * TE + TE > n) edge(s, stm, stn);
+  };
+  put_right(s0, 0);
   lstore(s0, lds);
-  if (nk == 1) note_min(0);
+  if (nk == 1) note(0);
   __syncthreads();
   uint32_t ctm = stm, ctn = stn, ck = 0, cseq = 0;  // the slice computed
   // Computes slice s from LDS, loads slice s + 2 into `in` and puts slice
@@ -621,7 +731,7 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
       ++sseq;
       tile_coords(tile0 + sseq, n, TE, stm, stn);
     }
-    if (ragged && sk == nk - 1 && more) fix(out, stm, stn);
+    if (more) put_right(out, sk);
     load(in);
     load_next(s + 3);
     __builtin_amdgcn_sched_barrier(0);
@@ -640,7 +750,7 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (sk == nk - 1 && more) note_min(sseq);
+    if (sk == nk - 1 && more) note(sseq);
     if (ck == nk - 1) {
       finish_tile(ctm, ctn, cseq);
       ++cseq;
@@ -660,26 +770,24 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
 
 // NBUF: LDS buffers (2, or 1 where the kernel variant has half the LDS).
 // One call computes `count` consecutive output tiles (row-major tile order)
-// of one product, as one stream of slices.  smem: NBUF x 36 KB and 24 bytes.
+// of one product, as one stream of slices.  smem: NBUF x 36 KB and the notes.
 template <int TE, int NBUF = 2>
 __device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A,
                                               const float* __restrict__ B,
                                               float* __restrict__ C, uint32_t n, uint32_t tile0,
                                               uint32_t count, lds_u8* smem) {
-  // smallest non-zero magnitude of the tile's A and B, as (bits << 1) - 1;
-  // three tiles in turn, so that one is cleared while the next is in use
-  CAF_LDS uint32_t(*s_min)[2] =
-      reinterpret_cast<CAF_LDS uint32_t(*)[2]>(smem + NBUF * kF32BufBytes);
+  // three tiles' notes in turn, so that one is cleared while the next is in use
+  CAF_LDS F32Note* s_note = reinterpret_cast<CAF_LDS F32Note*>(smem + NBUF * kF32BufBytes);
   const uint32_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(wave_id());
   if (n <= 32) {  // one block
     if (w == 0) gemm_f32_direct(A, B, C, n, 0, 0);
     __syncthreads();
     return;
   }
-  if (t < 6) s_min[t >> 1][t & 1u] = 0xFFFFFFFFu;
+  if (t < kF32NoteBytes / 4) reinterpret_cast<CAF_LDS uint32_t*>(s_note)[t] = 255u;
   __syncthreads();
-  if (w < 2) gemm_f32_stream<TE, NBUF, true>(A, B, C, n, tile0, count, smem, s_min);
-  else gemm_f32_stream<TE, NBUF, false>(A, B, C, n, tile0, count, smem, s_min);
+  if (w < 2) gemm_f32_stream<TE, NBUF, true>(A, B, C, n, tile0, count, smem, s_note);
+  else gemm_f32_stream<TE, NBUF, false>(A, B, C, n, tile0, count, smem, s_note);
 }
 
 // bfloat16 inputs: v_mfma_f32_32x32x16_bf16, k slices of kBf16SliceK.  Both operands

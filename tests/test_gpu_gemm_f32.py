@@ -116,3 +116,154 @@ def test_spread_magnitudes_are_no_further_off_than_one_rounding_per_term(sysm, n
     R, size = A @ B, np.abs(A) @ np.abs(B)
     rms = lambda x: float(np.sqrt((((x - R) / size) ** 2).mean()))
     assert rms(C) <= rms(chain.astype(np.float64)), (rms(C), rms(chain.astype(np.float64)))
+
+
+def _special(kind, n, g):
+    A, B = g.standard_normal((n, n)), g.standard_normal((n, n))
+    if kind == "one_tiny":  # one number in the subnormal range in each operand
+        A[n // 2, n // 3], B[n // 3, n // 2] = 1e-39, 1e-41
+    if kind == "softmax":  # tiny numbers next to ordinary ones, and rows of zeros
+        e = np.exp(40 * A)
+        A = e / e.sum(1, keepdims=True)
+        A[n // 2:n // 2 + 3] = 0
+    if kind == "products":  # outputs near the smallest normal number
+        A, B = A * 2.0 ** -60, B * 2.0 ** -60
+    if kind == "infinite":
+        A[n // 2, n // 3], B[n // 4, n // 5], A[0, 0] = np.inf, np.nan, 3.4e38
+    return A.astype(np.float32), B.astype(np.float32)
+
+
+KINDS = ["one_tiny", "softmax", "products", "infinite"]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_bits_do_not_depend_on_the_tile_edge_or_the_load(kind):
+    """The tile edge follows the load, and work tiles of several output tiles
+    run as one stream: neither may show in the product."""
+    import torch
+    from paper_1505_07368_amd import binding as cg
+    g = np.random.Generator(np.random.PCG64(5))
+    ins = {}
+    for n in (33, 65, 129, 130, 200, 257, 300):
+        A, B = _special(kind, n, g)
+        t = [torch.zeros(n * n + 1, device="cuda") for _ in range(2)]  # odd addresses
+        for x, v in zip(t, (A, B)):
+            x[1:] = torch.from_numpy(v).cuda().view(-1)
+        ins[n] = (A, B, t, [cg.caf_buf(x.data_ptr() + 4, n * n, cg.F32, 1) for x in t])
+    torch.cuda.synchronize()
+    first = {}
+    for kw in ({"gemm_tile": 64}, {"gemm_tile": 128}, {}, {"full_wgs_per_cu": 3},
+               {"mode": "plain"}):
+        with cg.System(**{"mode": "batched", "arena_bytes": 256 << 20, **kw}) as s:
+            a = s.spawn(cg.BHV_GEMM)
+            req = lambda n: s.request(a, cg.caf_gemm_args(n, cg.F32), inputs=ins[n][3])
+            got = [(n, req(n)) for n in ins]
+            if not kw:  # the same ones behind a queue, thirty times each
+                s.drain()
+                s.hold(True)
+                got += [(n, req(n)) for _ in range(30) for n in ins]
+                s.hold(False)
+            for n, f in got:
+                st, C = f.result()
+                assert st == cg.OK
+                bits = C.view(torch.int32).masked_fill(C.isnan(), 0x7FC00000)
+                if n not in first:
+                    first[n] = bits.clone()
+                    A, B = (x.astype(np.float64) for x in ins[n][:2])
+                    with np.errstate(all="ignore"):
+                        R, size = A @ B, np.abs(A) @ np.abs(B)
+                        off = np.abs(C.cpu().numpy().reshape(n, n).astype(np.float64) - R)
+                    ok = np.isfinite(R) & (np.abs(R) < 3.3e38)
+                    assert (off <= (n + 8) * 2.0 ** -24 * size + n * 2.0 ** -126)[ok].all(), (kind, n)
+                assert torch.equal(bits, first[n]), (kind, n, kw)
+                f.release()
+
+
+def test_small_numbers_next_to_ordinary_ones_take_no_longer():
+    """Products of a softmax matrix, whose smallest entries are far below the
+    ordinary ones, at the speed of others (twice their time allowed)."""
+    import time
+
+    import torch
+    from paper_1505_07368_amd import binding as cg
+    n, count = 512, 64
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    B = torch.randn(count, n, n, generator=g, device="cuda")
+    logits = 8 * torch.randn(count, n, n, generator=g, device="cuda")
+    out = torch.zeros(count, n * n, device="cuda")
+    with cg.System(mode="batched", arena_bytes=64 << 20) as s:
+        a = s.spawn(cg.BHV_GEMM)
+        args = np.zeros(1, cg.NP_GEMM)
+        args["n"], args["in_dtype"] = n, cg.F32
+
+        def took(A):
+            bufs = np.zeros((count, 2), cg.NP_BUF)
+            bufs["data"][:, 0] = A.data_ptr() + np.arange(count) * n * n * 4
+            bufs["data"][:, 1] = B.data_ptr() + np.arange(count) * n * n * 4
+            bufs["numel"], bufs["dtype"], bufs["on_device"] = n * n, cg.F32, 1
+            msgs = np.zeros(count, cg.NP_MSG)
+            msgs["actor"], msgs["n_in"] = a, 2
+            msgs["args"], msgs["args_bytes"] = args.ctypes.data, args.itemsize
+            msgs["in_"] = bufs.ctypes.data + np.arange(count, dtype=np.uint64) * bufs[0].nbytes
+            msgs["out"]["data"] = out.data_ptr() + np.arange(count) * n * n * 4
+            msgs["out"]["numel"], msgs["out"]["dtype"], msgs["out"]["on_device"] = n * n, cg.F32, 1
+            go, times = cg.PreparedDrive(s, msgs, count), []
+            torch.cuda.synchronize()
+            for _ in range(9):
+                t = time.perf_counter()
+                assert go() == cg.OK and not go.st.any()
+                times.append(time.perf_counter() - t)
+            return sorted(times)[4]
+
+        ordinary = took(torch.rand(count, n, n, generator=g, device="cuda") - 0.5)
+        assert took(torch.softmax(logits, 2)) <= 2 * ordinary
+
+
+@pytest.mark.parametrize("te,wgs", [(0, 2), (64, 2), (128, 2), (0, 3), (128, 3)])
+def test_streams_of_many_tiles(te, wgs):
+    """Many products in one launch, so that a claim holds several tiles: the
+    sizes' remainders at tile boundaries inside a stream, inputs one element
+    into an allocation, and numbers in some tiles that leave the others' way
+    (outputs that are not finite, operands of the subnormal range)."""
+    import torch
+    from paper_1505_07368_amd import binding as cg, gen
+    with cg.System(mode="batched", arena_bytes=1 << 30, gemm_tile=te, full_wgs_per_cu=wgs) as s:
+        a = s.spawn(cg.BHV_GEMM)
+        for code in (cg.F32, cg.BF16):
+            esz, keep, got = (4, 2)[code == cg.BF16], [], []
+            s.hold(True)
+            for n in (129, 200, 257, 300, 511):
+                g = np.random.Generator(np.random.PCG64(n))
+                A, B = (g.uniform(-1, 1, (n, n)).astype(np.float32) for _ in range(2))
+                if code == cg.BF16:
+                    A, B = (torch.from_numpy(x).bfloat16() for x in (A, B))
+                else:
+                    A[3, n - 1], A[n - 1, 0], B[5, n // 2] = np.inf, 1e-40, np.nan
+                    A[70] *= np.float32(1e-38)
+                    A, B = torch.from_numpy(A), torch.from_numpy(B)
+                bufs = []
+                for x in (A, B):
+                    t = torch.zeros(n * n + 1, dtype=x.dtype, device="cuda")
+                    t[1:] = x.cuda().view(-1)
+                    bufs.append(t)
+                torch.cuda.synchronize()
+                ins = [cg.caf_buf(t.data_ptr() + esz, n * n, code, 1) for t in bufs]
+                A, B = A.double(), B.double()
+                keep.append(bufs)
+                for _ in range(25):
+                    f = s.request(a, cg.caf_gemm_args(n, code), inputs=ins)
+                    got.append((n, f, A @ B, A.abs() @ B.abs()) if _ == 0 else (n, f, None, None))
+            s.hold(False)
+            for n, f, R, size in got:
+                st, C = f.result()
+                assert st == cg.OK
+                C = C.cpu().double().view(n, n)
+                if R is not None:
+                    first = C
+                    fin = torch.isfinite(R)
+                    off = (C - R).abs()
+                    assert (off <= (n + 8) * 2.0 ** -24 * size + n * 2.0 ** -126)[fin].all(), n
+                    assert (torch.isnan(C) == torch.isnan(R)).all(), n
+                assert torch.equal(C.nan_to_num(7.0), first.nan_to_num(7.0)), n
+                f.release()
