@@ -109,9 +109,10 @@ __device__ __forceinline__ bool actor_alive(const HostCtl* h, uint32_t actor) {
 
 // Publishes one reply notification to the host at completion position
 // `pos` (thread-level).  The message's reply is in memory by now (store_reply,
-// wait_stores and a barrier); what the record itself needs is waited for before
-// the word that makes it valid.  `inl`: the 16 bytes of a reply that travels
-// inline, else nullptr.
+// wait_stores and a barrier).  The word that makes the record valid also lets
+// the host hand the slot out again, so everything this thread stored before it
+// is waited for: the slot's counters and status, reset for the next message,
+// and the reply's bytes where it travels inline (`inl`: 16 bytes, else nullptr).
 __device__ __forceinline__ void write_completion_at(KArgsC& a, uint64_t pos, uint64_t req_id,
                                                     int32_t status, const uint64_t* inl) {
   Comp* c = &a.comp[pos & (a.ccap - 1u)];  // ccap is a power of two
@@ -119,8 +120,8 @@ __device__ __forceinline__ void write_completion_at(KArgsC& a, uint64_t pos, uin
     uint64_t* dst = reinterpret_cast<uint64_t*>(c->data);
     st_sys(dst, inl[0]);
     st_sys(dst + 1, inl[1]);
-    wait_stores();
   }
+  wait_stores();
   st_sys(&c->word, comp_word(req_id, status, (uint32_t)(pos >> __builtin_ctz(a.ccap)) + 1u));
 }
 
