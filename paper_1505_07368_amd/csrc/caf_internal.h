@@ -293,6 +293,8 @@ int cafgpu_request_tagged(caf_gpu_system* sys, caf_actor dst, uint32_t sender, c
 void cafgpu_help_begin(caf_gpu_system* sys);
 void cafgpu_help_end(caf_gpu_system* sys);
 bool cafgpu_poll_replies(caf_gpu_system* sys);
+// Releases a future inside a call on its system.
+void cafgpu_future_put(caf_gpu_system* sys, caf_future* f);
 bool cafgpu_blocking(const caf_gpu_system* sys);
 int64_t cafgpu_future_issue_ns(const caf_future* f);
 int64_t cafgpu_future_done_ns(const caf_future* f);

@@ -136,7 +136,7 @@ extern "C" int caf_gpu_drive(caf_gpu_system* sys, const caf_msg* msgs, uint64_t 
       ++live;
       return true;
     }
-    caf_future_release(p.prev);
+    cafgpu_future_put(sys, p.prev);
     p.prev = nullptr;
     fail(p.idx, st);
     free_tags.push_back(k);
@@ -160,7 +160,7 @@ extern "C" int caf_gpu_drive(caf_gpu_system* sys, const caf_msg* msgs, uint64_t 
     int32_t rs = CAF_OK;
     caf_future_poll(p.f, &res, &rs);
     if (p.prev) {
-      caf_future_release(p.prev);
+      cafgpu_future_put(sys, p.prev);
       p.prev = nullptr;
     }
     if (rs == CAF_OK && p.stage < chain_hops) {
@@ -176,7 +176,7 @@ extern "C" int caf_gpu_drive(caf_gpu_system* sys, const caf_msg* msgs, uint64_t 
     }
     if (status) status[p.idx] = rs;
     if (latency_ns) latency_ns[p.idx] = cafgpu_future_done_ns(p.f) - p.t_ref;
-    caf_future_release(p.f);
+    cafgpu_future_put(sys, p.f);
     p.f = nullptr;
     ++done;
     free_tags.push_back(k);
@@ -210,7 +210,7 @@ extern "C" int caf_gpu_drive(caf_gpu_system* sys, const caf_msg* msgs, uint64_t 
       // refused and its reply released, which lets the others go on.
       const uint32_t k = hop_wait[hop_head++ % window];
       Pending& p = pend[k];
-      caf_future_release(p.prev);
+      cafgpu_future_put(sys, p.prev);
       p.prev = nullptr;
       fail(p.idx, CAF_E_OVERLOAD);
       free_tags.push_back(k);

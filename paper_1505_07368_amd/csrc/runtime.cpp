@@ -187,7 +187,7 @@ size_t dtype_bytes(int32_t dt) {
 
 struct caf_future {
   std::atomic<caf_gpu_system*> sys{nullptr};  // null once the system is shut down
-  std::atomic<int> helping{0};  // waiters that may be using the system through it
+  std::atomic<int> helping{0};  // threads that may be using the system through it
   uint64_t req_id = 0;
   std::atomic<int> state{0};  // 0 pending, 1 replied, 2 gave up (timeout)
   int32_t status = 0;
@@ -337,13 +337,9 @@ caf_future* new_future(caf_gpu_system* s) {  // mu held
 }
 
 
-void put_ref(caf_future* f) {  // mu not held
+// mu not held; the caller keeps the system from going away meanwhile
+void put_ref(caf_gpu_system* s, caf_future* f) {
   if (f->refs.fetch_sub(1, std::memory_order_acq_rel) == 1) {
-    caf_gpu_system* s = f->sys.load(std::memory_order_relaxed);
-    if (!s) {  // orphaned by caf_gpu_shutdown
-      delete f;
-      return;
-    }
     caf_future* top = s->retired_futs.load(std::memory_order_relaxed);
     do {
       f->next_retired = top;
@@ -518,7 +514,7 @@ void resolve_batch(caf_gpu_system* s, const Comp* recs, uint32_t n) {
     } else {
       s->st_swallowed++;
     }
-    put_ref(f);
+    put_ref(s, f);
   }
   s->outstanding.fetch_sub(valid, std::memory_order_acq_rel);
   if (s->waiters.load(std::memory_order_relaxed)) s->cv_space.notify_all();
@@ -1147,6 +1143,9 @@ int cafgpu_request_tagged(caf_gpu_system* s, caf_actor dst, uint32_t sender, con
 void cafgpu_help_begin(caf_gpu_system* s) { s->helpers.fetch_add(1, std::memory_order_relaxed); }
 void cafgpu_help_end(caf_gpu_system* s) { s->helpers.fetch_sub(1, std::memory_order_relaxed); }
 bool cafgpu_poll_replies(caf_gpu_system* s) { return poll_replies(s); }
+void cafgpu_future_put(caf_gpu_system* s, caf_future* f) {
+  if (f) put_ref(s, f);
+}
 int64_t cafgpu_future_issue_ns(const caf_future* f) { return f->t_issue; }
 bool cafgpu_blocking(const caf_gpu_system* s) { return s->cfg.blocking != 0; }
 int64_t cafgpu_future_done_ns(const caf_future* f) { return f->t_done; }
@@ -1430,7 +1429,7 @@ int caf_future_wait(caf_future* f, int64_t timeout_ns, caf_buf* result, int32_t*
       }
       s->helpers.fetch_sub(1, std::memory_order_relaxed);
     }
-    f->helping.fetch_sub(1, std::memory_order_release);
+    f->helping.fetch_sub(1, std::memory_order_seq_cst);
   }
   for (;;) {
     if (caf_future_poll(f, result, reply_status) == 1)
@@ -1451,8 +1450,17 @@ int caf_future_wait(caf_future* f, int64_t timeout_ns, caf_buf* result, int32_t*
 
 uint64_t caf_future_id(const caf_future* f) { return f ? f->req_id : 0; }
 
+// Beside caf_gpu_shutdown: the system stays while `helping` is counted (as in
+// caf_future_wait), and so does the future, of which the shutdown holds a
+// reference from before it clears `sys` until after it saw no helper.  Once
+// `sys` is clear, the last reference deletes.
 void caf_future_release(caf_future* f) {
-  if (f) put_ref(f);
+  if (!f) return;
+  f->helping.fetch_add(1, std::memory_order_seq_cst);
+  caf_gpu_system* s = f->sys.load(std::memory_order_seq_cst);
+  if (s) put_ref(s, f);
+  f->helping.fetch_sub(1, std::memory_order_seq_cst);
+  if (!s && f->refs.fetch_sub(1, std::memory_order_acq_rel) == 1) delete f;
 }
 
 int caf_gpu_quit(caf_gpu_system* s, caf_actor actor, uint32_t /*exit_reason*/) {
@@ -1563,13 +1571,17 @@ int caf_gpu_shutdown(caf_gpu_system* s) {
     si = SlotInfo();
   }
   for (caf_future* f : s->all_futs) {
-    if (f->pooled || f->refs.load() <= 0) {
+    if (f->pooled) {
       delete f;
-    } else {
-      f->sys.store(nullptr, std::memory_order_seq_cst);
-      while (f->helping.load(std::memory_order_acquire)) std::this_thread::yield();
-      f->out = Block{};
+      continue;
     }
+    f->out = Block{};
+    f->refs.fetch_add(1, std::memory_order_acq_rel);
+    // a store and then a load of what the other side writes and reads the
+    // other way round: both seq_cst
+    f->sys.store(nullptr, std::memory_order_seq_cst);
+    while (f->helping.load(std::memory_order_seq_cst)) std::this_thread::yield();
+    if (f->refs.fetch_sub(1, std::memory_order_acq_rel) == 1) delete f;
   }
   for (auto& e : s->ev_pool) {
     hipEventDestroy(e.first);
