@@ -318,10 +318,12 @@ static_assert(smem_bytes(kBf16SliceK) >= 2 * kF32BufBytes + kF32NoteBytes &&
                   smem_bytes(32) >= kF32BufBytes + kF32NoteBytes,
               "fp32 tiles fit");
 
-// The square matrix tiles as calls, for the drain's full variant: inlined next
-// to the 128 x 256 tile their registers would spill.  Called from one kernel
-// only: with a second caller the calls save and restore the registers that
-// the tiles use (fp32 batch 2428 -> 2514 us).
+// The matrix tiles as calls, for the drain's full variant: inlined next to each
+// other their registers would spill, and with only the 128 x 256 tile inlined
+// what the kernel keeps for it is stored to scratch when a launch begins, for
+// the other calls (a lone product or matrix 42 -> 39 us without).  Called from
+// one kernel only: with a second caller the calls save and restore the
+// registers that the tiles use (fp32 batch 2428 -> 2514 us).
 __device__ __noinline__ void gemm_bf16_tile_call(const uint16_t* A, const uint16_t* B, float* C,
                                                  uint32_t n, uint32_t te, uint32_t tile,
                                                  uint32_t count, lds_u8* smem) {
@@ -333,6 +335,12 @@ __device__ __noinline__ void gemm_f32_tile_call(const float* A, const float* B, 
                                                 uint32_t count, lds_u8* smem) {
   if (te == 128) gemm_f32_tile<128>(A, B, C, n, tile, count, smem);
   else gemm_f32_tile<64>(A, B, C, n, tile, count, smem);
+}
+
+__device__ __noinline__ void gemm_bf16_tile_wide_call(const uint16_t* A, const uint16_t* B,
+                                                      float* C, uint32_t n, uint32_t tile,
+                                                      uint32_t count, lds_u8* smem) {
+  gemm_bf16_tile_wide(A, B, C, n, tile, count, smem);
 }
 
 // kFull = false compiles every behaviour except GEMM: without the matrix
@@ -392,7 +400,7 @@ __device__ __forceinline__ void run_tiles(KArgsC& a, const Desc& d, uint32_t til
         if (!(d.flags & DF_BF16))
           gemm_f32_tile_call(A, B, C, d.p.g.n, d.tcfg, t0, cnt, (lds_u8*)smem);
         else if (d.tcfg == 256)
-          gemm_bf16_tile_wide(A16, B16, C, d.p.g.n, t0, cnt, (lds_u8*)smem);
+          gemm_bf16_tile_wide_call(A16, B16, C, d.p.g.n, t0, cnt, (lds_u8*)smem);
         else
           gemm_bf16_tile_call(A16, B16, C, d.p.g.n, d.tcfg, t0, cnt, (lds_u8*)smem);
       } else if (d.tcfg == 256) {
