@@ -925,7 +925,15 @@ int submit(caf_gpu_system* s, caf_actor dst, uint32_t sender, const void* args,
     return CAF_E_INVALID;
   Desc d;
   fill_desc(s, a, aidx, args, in, inline_in, inline_out, is_request, &d);
-  if (desc_ntiles(d) > kTileMapCap / 4) return CAF_E_INVALID;
+  {
+    // The largest message has a quarter of the tile map's entries, counted in
+    // the smallest tiles its actor may use: what is refused depends neither on
+    // the load nor on its iteration count.
+    Desc smallest = d;
+    if (d.behavior == CAF_BHV_MANDELBROT) smallest.tcfg = s->mandel_tile_px;
+    if (d.behavior == CAF_BHV_TANH || d.behavior == CAF_BHV_ROWSUM) smallest.tcfg = 0;
+    if (desc_ntiles(smallest) > kTileMapCap / 4) return CAF_E_INVALID;
+  }
   for (uint32_t h = 0; h < nhops; ++h)
     d.hop_actor[h] = ((uint32_t)hbeh[h] << 16) | (hidx[h] + 1);
 

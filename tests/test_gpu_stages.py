@@ -88,3 +88,21 @@ def test_matrices_of_several_tiles_per_claim(sysm, rows, cols):
     assert ((out.double() - t).abs() <= 4 * ULP * t.abs()).all()
     xd = x.double().view(rows, cols)
     assert ((got[1][1].double() - xd.sum(1)).abs() <= (cols + 8) * ULP / 2 * xd.abs().sum(1)).all()
+
+
+@pytest.mark.parametrize("mode", ["plain", "batched"])
+def test_messages_of_too_many_tiles_are_refused(mode):
+    """A message has at most 2^20 tiles, of 4096 elements, 16 rows or 1024
+    pixels (512 in plain mode), whatever tiles it would be cut into.  (Their replies exceed the
+    arena too, which is another refusal.)"""
+    import torch
+    from paper_1505_07368_amd import binding as cg
+    few = torch.zeros(16, device="cuda")
+    with cg.System(mode=mode, arena_bytes=16 << 20) as s:
+        for bhv, rows, cols in ((cg.BHV_TANH, 65537, 65536), (cg.BHV_ROWSUM, (1 << 24) + 16, 1)):
+            buf = cg.caf_buf(few.data_ptr(), rows * cols, cg.F32, 1)
+            rc, f = s.request_raw(s.spawn(bhv), cg.caf_shape_args(rows, cols), inputs=[buf])
+            assert rc == cg.E_INVALID and f is None, (bhv, rc)
+        big = cg.caf_mandel_args(-2.0, -1.0, 1e-6, 1e-6, 1 << 20, 1025, 0, 1025, 10, cg.F32)
+        rc, f = s.request_raw(s.spawn(cg.BHV_MANDELBROT), big)
+        assert rc == cg.E_INVALID and f is None, rc
