@@ -651,6 +651,12 @@ int check_signature(const ActorRec& a, const void* args, uint64_t args_bytes, co
   return CAF_E_INVALID;
 }
 
+// The drain launches of this system run the full variant (a launch per message
+// has kernels of its own, of which only the products' is full).
+bool full_launches(const caf_gpu_system* s) {
+  return !s->plain() && s->need_full.load(std::memory_order_relaxed);
+}
+
 // Tile choice of a product (tcfg): 256 stands for 128 x 256 bf16 tiles, for
 // n % 32 == 0 and 16-byte aligned device inputs (host inputs are staged into
 // the arena, which is), in the ring modes with two full workgroups per compute
@@ -716,7 +722,9 @@ uint32_t gemm_unit_for(const caf_gpu_system* s, uint32_t tiles, bool bf16, uint6
 // 1024, 114 with 2048; a 1021 x 773 one at 300 116 and 157), or an eighth
 // once 32 are out, or if 48 messages of at most 4096 pixels are (4,096 of
 // 64 x 64 at 100 in a window of 256 1159 and 1003; 180 of 67 x 67 at 267,
-// which this leaves at 1024, 121 and 163).
+// which this leaves at 1024, 121 and 163).  The grid is the light variant's,
+// also where a full one runs: with the full one's, which is smaller, one
+// 1920 x 1080 image at 100 got tiles of 4096 and took 110 us instead of 100.
 uint32_t mandel_tile_for(const caf_gpu_system* s, const caf_mandel_args* m, uint64_t ahead) {
   uint32_t t = s->mandel_tile_px;
   if (s->cfg.mandel_tile_px || s->plain()) return t;
@@ -734,21 +742,28 @@ uint32_t mandel_tile_for(const caf_gpu_system* s, const caf_mandel_args* m, uint
 
 // Work tiles of an elementwise or row message.  While memory is busy a claim
 // waits for it too (its four dependent round trips took 34 us, a tile's own
-// work 25), so a large matrix is cut into one tile for half of the light
-// variant's workgroups, and two messages run side by side without a second
-// claim (8192 x 4100 through both actors: 286 us with four times as many
-// tiles, 219 with twice as many, 127 with these, 139 and 167 with two thirds
-// and half of them).  A small one is cut into the smallest tiles: 4096
-// elements, or four rows and at least 4096 elements of them.
-void stage_tiles(const caf_gpu_system* s, Desc* d) {
+// work 25), so the messages out together are cut into one tile for each
+// workgroup of the variant that runs, and a large matrix alone into one for
+// half of the light variant's (8192 x 4100 through both actors: 286 us with
+// four times as many tiles, 219 with twice as many, 127 with these, 139 and
+// 167 with two thirds and half of them; 64 messages of 1000 x 1000, row sums
+// 360 -> 183 us and tanh 604 -> 278 in the light variant, where each message
+// was cut as if alone).  A small one is cut into the smallest tiles: 4096
+// elements, or as many rows as a workgroup's waves load at once (four, sixteen
+// in the full variants: 64 messages of 64 x 16384 100 -> 61 us) and at least
+// 4096 elements of them.
+void stage_tiles(const caf_gpu_system* s, Desc* d, uint64_t ahead) {
   const uint64_t ne = (uint64_t)d->p.s.rows * d->p.s.cols;
-  const uint64_t half = std::max<uint64_t>(1, s->grid_light / 2);
-  const uint64_t per = std::max<uint64_t>(kTanhTile, (ne + half - 1) / half);  // elements per tile
+  const bool full = full_launches(s);
+  const uint64_t grid = full ? s->grid_full : s->grid_light;
+  const uint64_t alone = std::max<uint64_t>(1, full ? grid : grid / 2);
+  const uint64_t per = std::max<uint64_t>({kTanhTile, (ne + alone - 1) / alone,
+                                           (ahead + 1) * ne / grid});  // elements per tile
   if (d->behavior == CAF_BHV_TANH) {
     d->tcfg = (uint32_t)std::min<uint64_t>(64, (per + kTanhTile - 1) / kTanhTile);
   } else {
-    const uint64_t rows = (per + d->p.s.cols - 1) / d->p.s.cols;
-    d->tcfg = (uint32_t)std::min<uint64_t>(1u << 16, (rows + 3) / 4 * 4);
+    const uint64_t rows = (per + d->p.s.cols - 1) / d->p.s.cols, step = full ? 16 : 4;
+    d->tcfg = (uint32_t)std::min<uint64_t>(8192, (rows + step - 1) / step * step);
   }
 }
 
@@ -802,7 +817,7 @@ void fill_desc(const caf_gpu_system* s, const ActorRec& a, uint32_t aidx, const 
       const caf_shape_args* x = (const caf_shape_args*)args;
       d->p.s.rows = x->rows;
       d->p.s.cols = x->cols;
-      stage_tiles(s, d);
+      stage_tiles(s, d, s->plain() ? 0 : s->outstanding.load(std::memory_order_relaxed));
       break;
     }
     case CAF_BHV_HASHCHAIN:

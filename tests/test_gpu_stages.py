@@ -106,3 +106,39 @@ def test_messages_of_too_many_tiles_are_refused(mode):
         big = cg.caf_mandel_args(-2.0, -1.0, 1e-6, 1e-6, 1 << 20, 1025, 0, 1025, 10, cg.F32)
         rc, f = s.request_raw(s.spawn(cg.BHV_MANDELBROT), big)
         assert rc == cg.E_INVALID and f is None, rc
+
+
+@pytest.mark.parametrize("gemm,wgs", [(False, 0), (True, 2), (True, 3)])
+def test_tiles_follow_the_load_and_the_variant(gemm, wgs):
+    """Work tiles grow with the messages out, and are cut for the drain
+    variant that runs (a GEMM actor exists or not): the same matrices alone
+    and behind a queue, whose last tiles are partial, of rows shorter than a
+    vector, of few long rows."""
+    import torch
+    from paper_1505_07368_amd import binding as cg
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    with cg.System(mode="batched", arena_bytes=1 << 30, full_wgs_per_cu=wgs) as s:
+        if gemm:
+            s.spawn(cg.BHV_GEMM)
+        th, rs = s.spawn(cg.BHV_TANH), s.spawn(cg.BHV_ROWSUM)
+        cases = []
+        for rows, cols in ((257, 1001), (13, 16384), (70001, 1), (5003, 63)):
+            x = torch.rand(rows * cols, generator=g, device="cuda") * 4 - 2
+            torch.cuda.synchronize()
+            cases.append((rows, cols, x, x.double().view(rows, cols)))
+        for copies in (1, 24):
+            s.hold(True)
+            futs = [(c, s.request(th, cg.caf_shape_args(*c[:2]), inputs=[c[2]]),
+                     s.request(rs, cg.caf_shape_args(*c[:2]), inputs=[c[2]]))
+                    for _ in range(copies) for c in cases]
+            s.hold(False)
+            for (rows, cols, _, ref), ft, fr in futs:
+                (st, t), (sr, r) = ft.result(), fr.result()
+                assert st == cg.OK and sr == cg.OK
+                want = torch.tanh(ref)
+                assert ((t.double().view(rows, cols) - want).abs() <= 4 * ULP * want.abs()).all()
+                off = (r.double() - ref.sum(1)).abs()
+                assert (off <= (cols + 8) * 2.0 ** -24 * ref.abs().sum(1)).all(), (rows, cols)
+                ft.release()
+                fr.release()
