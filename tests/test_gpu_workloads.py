@@ -518,3 +518,21 @@ def test_gemm_sizes_each_full_variant(dtype, wgs):
             assert st == cg.OK, (n, st)
             err = rel_fro(C.cpu().numpy().reshape(n, n), oracle.gemm(A, B, dtype))
             assert err <= 1e-5, (n, err)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_autotuner_may_leave_the_tile_to_the_load(monkeypatch, dtype):
+    """Where no fixed tile edge is faster, a size class keeps the library's
+    own choice; a faster one is taken."""
+    import torch
+    from paper_1505_07368_amd import autotune
+    monkeypatch.setattr(autotune, "_time_drive", lambda *a: 1.0)
+    assert autotune.tune_gemm(torch, dtype=dtype, count_per_size=2) == [0, 0, 0, 0]
+    times = iter([1.0, 0.9, 0.95] + [0.96] * (dtype == "bf16"))
+    last = [1.0]
+
+    def faster(*a):
+        last[0] = next(times, last[0])
+        return last[0]
+    monkeypatch.setattr(autotune, "_time_drive", faster)
+    assert autotune.tune_gemm(torch, dtype=dtype, count_per_size=2)[0] == 64
