@@ -657,25 +657,28 @@ bool full_launches(const caf_gpu_system* s) {
   return !s->plain() && s->need_full.load(std::memory_order_relaxed);
 }
 
-// Tile choice of a product (tcfg): 256 stands for 128 x 256 bf16 tiles, for
-// n % 32 == 0 and 16-byte aligned device inputs (host inputs are staged into
-// the arena, which is), in the ring modes with two full workgroups per compute
-// unit (their LDS holds the tile's three stages).  A system whose configuration names 256
-// anywhere gives them to every product that qualifies; other products get
-// their class's edge, 128 where that is 256.
+// Tile choice of a product (tcfg).
 //
-// Without a choice by the caller, the tile follows the load: `ahead` messages
-// are out and not answered.  128 x 256 read fewer operand bytes and are used
-// when the products together fill the grid with them (148 products of
-// n = 512 141 us against 176 with 128 x 128, one of 4096 198 against 241; but
-// two of 2048 110 against 81).  An fp32 product alone, or with the 128-tiles
-// of all of them filling less than an eighth of the grid (the first of a
-// burst would be cut small otherwise), is cut into 64-tiles (one product
-// alone: n = 256 28 against 36 us, 1024 69 against 116, 1536 132 against 170;
-// at 2048 193 against 208, but two at once 315 against 237); with the chip
-// busy 128 is better from n = 65 on (1,024 products of 128: 168 against
-// 256 us).  bf16 tiles are short: 128 always.  The tile does not change the
-// sums.
+// The rule, with `ahead` messages out and not answered:
+//   256 (128 x 256 bf16 tiles; n % 32 == 0, 16-byte aligned device inputs --
+//     host inputs are staged into the arena, which is --, ring modes with two
+//     full workgroups per compute unit, whose LDS holds the tile's three
+//     stages): every product that qualifies if the configuration names 256
+//     anywhere; without a choice by the caller those with n > 64, once the
+//     products out fill the grid with such tiles;
+//   64: fp32 with three workgroups per compute unit (run_tiles); n <= 64; and
+//     an fp32 product alone of less than a third of the grid in 128-tiles, or
+//     several of less than an eighth (the first of a burst would be cut small
+//     otherwise);
+//   the caller's edge (128 where that is 256), or 128.
+// The tile does not change the sums.
+//
+// Measured (us).  128 x 256 reads fewer operand bytes: 148 bf16 products of
+// n = 512 136, with 128 x 128 179; one of 4096 209 and 223; but two of 2048
+// 119 and 91.  fp32, 64-tiles and 128-tiles: one product alone of n = 256 44
+// and 51, of 1024 86 and 139, of 1536 147 and 195, of 2048 240 and 265, but
+// two of 2048 at once 435 and 297; 1,024 products of 128 192 and 163.  bf16
+// tiles are short: one product of 1024 56 and 54.
 uint32_t gemm_tile_for(const caf_gpu_system* s, const caf_gemm_args* g, const caf_buf* in,
                        uint64_t ahead) {
   const uint32_t n = g->n;
@@ -713,18 +716,22 @@ uint32_t gemm_unit_for(const caf_gpu_system* s, uint32_t tiles, bool bf16, uint6
 }
 
 // Pixels per work tile of an escape-time message where the caller leaves the
-// choice: 1024, and twice or four times that where a tile is cheap next to its
-// claim (some microseconds, more with all workgroups claiming).  A tile may
-// have 1.7e6 pixel iterations (half as many in double) if the messages out
-// fill the grid with such tiles (1,024 tiles of 128 x 128 at max_iter 400
-// 1002 us with 1024, 649 with 4096; the image batch at 1000 1741 and 1887),
-// and 4.5e5 if they fill half of it (one 1920 x 1080 image at 120 139 us with
-// 1024, 114 with 2048; a 1021 x 773 one at 300 116 and 157), or an eighth
-// once 32 are out, or if 48 messages of at most 4096 pixels are (4,096 of
-// 64 x 64 at 100 in a window of 256 1159 and 1003; 180 of 67 x 67 at 267,
-// which this leaves at 1024, 121 and 163).  The grid is the light variant's,
-// also where a full one runs: with the full one's, which is smaller, one
-// 1920 x 1080 image at 100 got tiles of 4096 and took 110 us instead of 100.
+// choice: 1024, doubled up to 4096 while a tile stays cheap next to its claim
+// (some microseconds, more with all workgroups claiming) and enough are left.
+//
+// The rule.  A doubled tile may have
+//   1.7e6 pixel iterations (half as many in double) if the messages out fill
+//     the grid with such tiles;
+//   4.5e5 if they fill half of it, or an eighth once 32 are out, or if 48
+//     messages of at most 4096 pixels are.
+//
+// Measured (us, 1024 pixels and the larger tile): 1,024 tiles of 128 x 128 at
+// max_iter 400 1002 and 649, the image batch at 1000 1741 and 1887 (above the
+// first limit); one 1920 x 1080 image at 120 139 and 114, a 1021 x 773 one at
+// 300 116 and 157 (above the second); 4,096 of 64 x 64 at 100 in a window of
+// 256 1159 and 1003, 180 of 67 x 67 at 267 121 and 163.  The grid is the light
+// variant's, also where a full one runs: with the full one's, which is
+// smaller, one 1920 x 1080 image at 100 got 4096 and took 110 instead of 100.
 uint32_t mandel_tile_for(const caf_gpu_system* s, const caf_mandel_args* m, uint64_t ahead) {
   uint32_t t = s->mandel_tile_px;
   if (s->cfg.mandel_tile_px || s->plain()) return t;

@@ -457,7 +457,7 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
   };
   zero_acc();
 
-  const uint32_t nk = (n + KS - 1) / KS;  // slices per tile
+  const uint32_t nk = (n + KS - 1) / KS;  // slices per tile: two or more, n > 32
   const uint32_t steps = count * nk;
   // What a thread loads of a slice.  A: four rows TE / 4 apart, 4 k each (the
   // lanes of a row side by side).  B: a block of 4 k x 4 columns.
@@ -710,7 +710,7 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
   tile_coords(tile0, n, TE, stm, stn);
   load(s0);
   load_next(1);
-  load(s1);  // with a single slice, that slice again
+  load(s1);
   load_next(2);
   auto put_right = [&](Slice& s, uint32_t k) {  // slice k of tile (stm, stn)
     if (ragged && k == nk - 1) fix(s, stm, stn);
@@ -718,7 +718,6 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
   };
   put_right(s0, 0);
   lstore(s0, lds);
-  if (nk == 1) note(0);
   __syncthreads();
   uint32_t ctm = stm, ctn = stn, ck = 0, cseq = 0;  // the slice computed
   // Computes slice s from LDS, loads slice s + 2 into `in` and puts slice
@@ -1014,8 +1013,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const uint16_t* __restrict__ A, c
 // wider block reads a quarter fewer operand bytes per flop than two 128 x 128
 // tiles; a batch of mixed products is bound by those reads from beyond L2
 // (each tile re-reads the A and B panels it shares with its neighbours).
-// They run in a drain variant of their own, whose other matrix tiles are
-// out of line: inlined next to these, their registers would spill.
+// The drain's variant with two workgroups per compute unit has them, as a call
+// beside the other matrix tiles.
 //
 // Operands go from global memory straight into a three-stage LDS ring
 // (global_load_lds_dwordx4: 16 bytes per lane, laid out lane by lane per wave

@@ -38,3 +38,28 @@ def test_bound_over_sizes(te, wgs, offset):
             off = np.abs(C - Af @ Bf)
             bound = (n + 2) * 2.0 ** -24 * (np.abs(Af) @ np.abs(Bf))
             assert (off <= bound).all(), (n, float((off / bound).max()))
+
+
+def test_bits_do_not_depend_on_the_tile():
+    """The tile follows the load (64, 128 or 128 x 256, with 64- or 32-deep
+    slices): magnitudes spread over 2^-20 to 2^20 have the same sums in all."""
+    import torch
+    from paper_1505_07368_amd import binding as cg
+    g = torch.Generator(device="cuda")
+    first = {}
+    for kw in ({"gemm_tile": 64}, {"gemm_tile": 128}, {"gemm_tile": 256}, {"full_wgs_per_cu": 3},
+               {"mode": "plain"}):
+        with cg.System(**{"mode": "batched", "arena_bytes": 64 << 20, **kw}) as s:
+            a = s.spawn(cg.BHV_GEMM)
+            for n in (64, 96, 130, 160, 257, 512):
+                g.manual_seed(n)
+                A, B = ((torch.randn(n * n, generator=g, device="cuda") * torch.exp2(
+                    40 * torch.rand(n * n, generator=g, device="cuda") - 20)).bfloat16()
+                    for _ in range(2))
+                torch.cuda.synchronize()
+                f = s.request(a, cg.caf_gemm_args(n, cg.BF16), inputs=[A, B])
+                st, C = f.result()
+                assert st == cg.OK
+                bits = C.view(torch.int32)
+                assert torch.equal(bits, first.setdefault(n, bits.clone())), (kw, n)
+                f.release()
