@@ -755,17 +755,20 @@ uint32_t mandel_tile_for(const caf_gpu_system* s, const caf_mandel_args* m, uint
 // four times as many tiles, 219 with twice as many, 127 with these, 139 and
 // 167 with two thirds and half of them; 64 messages of 1000 x 1000, row sums
 // 360 -> 183 us and tanh 604 -> 278 in the light variant, where each message
-// was cut as if alone).  A small one is cut into the smallest tiles: 4096
-// elements, or as many rows as a workgroup's waves load at once (four, sixteen
-// in the full variants: 64 messages of 64 x 16384 100 -> 61 us) and at least
-// 4096 elements of them.
+// was cut as if alone) -- but none into fewer than four for the others' sake,
+// which its own reply would wait for (host-mediated chains of 128 x 128
+// matrices, 1,024 in flight: 1.6M a second with single tiles, 1.9M with four).
+// A small one is cut into the smallest tiles: 4096 elements, or as many rows
+// as a workgroup's waves load at once (four, sixteen in the full variants: 64
+// messages of 64 x 16384 100 -> 61 us) and at least 4096 elements of them.
 void stage_tiles(const caf_gpu_system* s, Desc* d, uint64_t ahead) {
   const uint64_t ne = (uint64_t)d->p.s.rows * d->p.s.cols;
   const bool full = full_launches(s);
   const uint64_t grid = full ? s->grid_full : s->grid_light;
   const uint64_t alone = std::max<uint64_t>(1, full ? grid : grid / 2);
+  // elements per tile
   const uint64_t per = std::max<uint64_t>({kTanhTile, (ne + alone - 1) / alone,
-                                           (ahead + 1) * ne / grid});  // elements per tile
+                                           std::min((ahead + 1) * ne / grid, ne / 4)});
   if (d->behavior == CAF_BHV_TANH) {
     d->tcfg = (uint32_t)std::min<uint64_t>(64, (per + kTanhTile - 1) / kTanhTile);
   } else {
