@@ -320,9 +320,11 @@ __device__ __forceinline__ void store_c(CAF_GLOBAL float* C, uint32_t n, uint32_
 // 0.39 / 0.58), and those products are one block: they take the fp32
 // instructions.
 // Products in a batch, 256 of n = 512: 815 us with the fp32 instructions,
-// 650 us (106 TFLOP/s); 4,096 of 64 .. 512 3455 -> 2800.  The matrix
-// instructions bound it: the clock drops to 1.7 GHz under them, and an eighth
-// of the 1.3 PFLOP/s that large bf16 products reach is 163 TFLOP/s.
+// 650 us (106 TFLOP/s); 4,096 of 64 .. 512 3455 -> 2800.  The clock drops to
+// 1.7 GHz under the matrix instructions, which are under way in half of its
+// cycles in that mix (an eighth of the 1.3 PFLOP/s that large bf16 products
+// reach would be 163 TFLOP/s); the rest is the slices' barriers and operand
+// reads, 3.5 times the operands' bytes from beyond the L2.
 //
 // The split is exact only while no term underflows, and a value near the top
 // of the range rounds to infinity.  So a 32 x 32 block of C is redone with
