@@ -333,10 +333,11 @@ __device__ __forceinline__ void store_c(CAF_GLOBAL float* C, uint32_t n, uint32_
 // (F32Note) and one of its outputs is so small that these bits could show.
 // Infinities, NaNs, tiny and huge inputs come out as those instructions give
 // them; a softmax or a Gaussian kernel matrix, which holds tiny numbers next
-// to ordinary ones, is not redone (128 products of n = 512: 390 us as for
-// U(-1, 1) entries, 1525 us when every 128-tile with a product of entries
-// below 2^-100 was redone).  Where every output is about as small as fp32
-// holds (1e-33) the whole product is: 885 us, 475 with fp32 instructions only.
+// to ordinary ones, is not redone (128 products of n = 512: 400 us as for
+// U(-1, 1) entries, 1490 us when every 128-tile with a product of entries
+// below 2^-100 was redone, 480 with fp32 instructions only).  Where every
+// output is about as small as fp32 holds, below 2^-122, the whole product is:
+// 930 us, 485 with fp32 instructions only.
 // What is noted does not depend on the tile edge, nor does any sum: the same
 // product has the same bits whatever the load chose.
 //
@@ -665,15 +666,17 @@ __device__ __forceinline__ void gemm_f32_stream(const float* __restrict__ A,
         if (__builtin_amdgcn_ballot_w64(!(any[0] + any[1] == 0.f))) redo |= 1u << (i * WB + j);
       }
     if (__builtin_expect(lossy, 0)) {
-      // 2^24 times what the split may have lost of an output: n 2^-134 of
-      // the other operand's largest for small elements, and n 2^-146
+      // What the split may have lost of an output, per k: 2^-134 of the other
+      // operand's largest for small elements, and 2^-146.  It is nothing next
+      // to the rounding of a sum, 2^-24 of its magnitude per k, where the
+      // output alone is 2^24 times as large.
       auto largest = [](uint32_t inv) {  // 2^(exponent + 1) of the biased one, finite
         return __builtin_bit_cast(float, min(255u - inv + 1u, 254u) << 23);
       };
       const float ma = largest(__builtin_amdgcn_readfirstlane(nt.a[ha][1])),
                   mb = largest(__builtin_amdgcn_readfirstlane(nt.b[hb][1]));
-      const float lost = (float)n * (0x1p-110f * ((ea < kSplitMinExp ? mb : 0.f) +
-                                                  (eb < kSplitMinExp ? ma : 0.f)) + 0x1p-122f);
+      const float lost = 0x1p-110f * ((ea < kSplitMinExp ? mb : 0.f) +
+                                      (eb < kSplitMinExp ? ma : 0.f)) + 0x1p-122f;
 #pragma unroll
       for (uint32_t i = 0; i < WB; ++i)
 #pragma unroll
