@@ -777,6 +777,28 @@ void stage_tiles(const caf_gpu_system* s, Desc* d, uint64_t ahead) {
   }
 }
 
+// The largest message has a quarter of the tile map's entries, counted in the
+// smallest tiles its actor may use: what is refused depends neither on the
+// load nor on its iteration count.  (A product has at most 2^16 tiles; an
+// image a tile per eight pixels at worst, where its blocks are mostly padding.)
+bool too_many_tiles(const caf_gpu_system* s, const Desc& d) {
+  constexpr uint64_t most = kTileMapCap / 4;
+  switch (d.behavior) {
+    case CAF_BHV_MANDELBROT: {
+      if ((uint64_t)d.p.m64.rows * d.p.m64.width <= 4 * most) return false;
+      Desc smallest = d;
+      smallest.tcfg = s->mandel_tile_px;
+      return desc_ntiles(smallest) > most;
+    }
+    case CAF_BHV_TANH:
+      return (uint64_t)d.p.s.rows * d.p.s.cols > most * kTanhTile;
+    case CAF_BHV_ROWSUM:
+      return d.p.s.rows > most * kRowsumTile;
+    default:
+      return false;
+  }
+}
+
 // Builds the descriptor of the first stage (all fields except slot, seq and
 // request id).
 void fill_desc(const caf_gpu_system* s, const ActorRec& a, uint32_t aidx, const void* args,
@@ -950,15 +972,7 @@ int submit(caf_gpu_system* s, caf_actor dst, uint32_t sender, const void* args,
     return CAF_E_INVALID;
   Desc d;
   fill_desc(s, a, aidx, args, in, inline_in, inline_out, is_request, &d);
-  {
-    // The largest message has a quarter of the tile map's entries, counted in
-    // the smallest tiles its actor may use: what is refused depends neither on
-    // the load nor on its iteration count.
-    Desc smallest = d;
-    if (d.behavior == CAF_BHV_MANDELBROT) smallest.tcfg = s->mandel_tile_px;
-    if (d.behavior == CAF_BHV_TANH || d.behavior == CAF_BHV_ROWSUM) smallest.tcfg = 0;
-    if (desc_ntiles(smallest) > kTileMapCap / 4) return CAF_E_INVALID;
-  }
+  if (too_many_tiles(s, d)) return CAF_E_INVALID;
   for (uint32_t h = 0; h < nhops; ++h)
     d.hop_actor[h] = ((uint32_t)hbeh[h] << 16) | (hidx[h] + 1);
 
