@@ -179,9 +179,11 @@ def test_bits_do_not_depend_on_the_tile_edge_or_the_load(kind):
                 f.release()
 
 
-def test_small_numbers_next_to_ordinary_ones_take_no_longer():
+@pytest.mark.parametrize("kind", ["softmax", "tiny"])
+def test_small_numbers_take_no_longer(kind):
     """Products of a softmax matrix, whose smallest entries are far below the
-    ordinary ones, at the speed of others (twice their time allowed)."""
+    ordinary ones, and of numbers about 1e-20 and 1e-14, at the speed of others
+    (twice their time allowed)."""
     import time
 
     import torch
@@ -217,7 +219,26 @@ def test_small_numbers_next_to_ordinary_ones_take_no_longer():
             return sorted(times)[4]
 
         ordinary = took(torch.rand(count, n, n, generator=g, device="cuda") - 0.5)
-        assert took(torch.softmax(logits, 2)) <= 2 * ordinary
+        if kind == "softmax":
+            A = torch.softmax(logits, 2)
+        else:
+            A, B = logits * 1e-20, B * 1e-14
+        assert took(A) <= 2 * ordinary
+
+
+@pytest.mark.parametrize("n", [33, 130, 257])
+@pytest.mark.parametrize("e", [50, 54, 56, 58, 60, 62])
+def test_outputs_near_the_smallest_numbers(sysm, n, e):
+    """Operands about 2^-e: outputs from 2^-96 down to 2^-124, on both sides of
+    the line below which blocks are redone.  What the split may lose there is
+    2^-146 per k."""
+    g = np.random.Generator(np.random.PCG64(n + e))
+    A, B = ((g.standard_normal((n, n)) * 2.0 ** -e).astype(np.float32) for _ in range(2))
+    C = _product(sysm, A, B).astype(np.float64)
+    A, B = A.astype(np.float64), B.astype(np.float64)
+    bound = (n + 8) * 2.0 ** -24 * (np.abs(A) @ np.abs(B)) + n * 2.0 ** -146
+    off = np.abs(C - A @ B)
+    assert (off <= bound).all(), float((off / bound).max())
 
 
 @pytest.mark.parametrize("te,wgs", [(0, 2), (64, 2), (128, 2), (0, 3), (128, 3)])
